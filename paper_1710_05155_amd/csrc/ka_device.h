@@ -544,5 +544,136 @@ __device__ __forceinline__ void vertical_count(u64 x, unsigned &acc)
   acc += (unsigned)__popcll(x);
 }
 
+// ------------------------------------------------------------------------------------
+// The same counts over many words.  Every lane adds its words into a bit-sliced
+// counter (plane k holds bit k of the 64 per-replica sums): four words go in with three
+// carry-save adders and a ripple of half adders, about 8 VALU instructions per word, and only
+// the planes, not the words, are transposed and counted, once per kMaxWords words.
+// ------------------------------------------------------------------------------------
+struct LaneCounter {
+  static constexpr int kPlanes = 7;
+  static constexpr int kMaxWords = 124;   // multiple of 4 below 2^kPlanes
+  u64 c[kPlanes];
+
+  __device__ __forceinline__ void clear()
+  {
+#pragma unroll
+    for (int k = 0; k < kPlanes; ++k) c[k] = 0;
+  }
+
+  __device__ __forceinline__ void add4(u64 a, u64 b, u64 d, u64 e)
+  {
+    u64 t0, t1, f;
+    full_add(c[0], a, b, c[0], t0);
+    full_add(c[0], d, e, c[0], t1);
+    full_add(c[1], t0, t1, c[1], f);
+#pragma unroll
+    for (int k = 2; k < kPlanes; ++k) {
+      const u64 carry = c[k] & f;
+      c[k] ^= f;
+      f = carry;
+    }
+  }
+};
+
+// x of lane (this ^ S), S a power of two below 32.
+template <int S>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t x)
+{
+  static_assert(S == 1 || S == 2 || S == 4 || S == 8 || S == 16, "lanes of one half of the wave");
+  if constexpr (S == 1) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xF, 0xF, true);        // quad_perm 1,0,3,2
+  else if constexpr (S == 2) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xF, 0xF, true);   // quad_perm 2,3,0,1
+  else if constexpr (S == 8) return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xF, 0xF, true);  // row_ror:8
+  else return (uint32_t)__builtin_amdgcn_ds_swizzle((int)x, (S << 10) | 0x1F);
+}
+
+// One butterfly stage of the 32 x 32 bit transpose (lanes of each half of the wave): lanes l and
+// l ^ S swap their off-diagonal S x S blocks.  The partner's word is rotated by S towards this
+// lane's missing columns and merged in under the lane's mask.
+template <int S>
+__device__ __forceinline__ uint32_t transpose_stage(uint32_t x, int lane)
+{
+  constexpr uint32_t m = S == 16 ? 0x0000FFFFu : S == 8 ? 0x00FF00FFu : S == 4 ? 0x0F0F0F0Fu : S == 2 ? 0x33333333u : 0x55555555u;
+  const bool up = (lane & S) != 0;
+  const uint32_t keep = up ? ~m : m;
+  const uint32_t y = lane_xor<S>(x);
+  const uint32_t r = __builtin_amdgcn_alignbit(y, y, up ? (uint32_t)S : (uint32_t)(32 - S));
+  return (x & keep) | (r & ~keep);
+}
+
+// Adds to acc the number of the wave's words counted into `n` whose bit `lane` is set; `n` holds
+// at most `words` per lane (wave-uniform).  Lanes l and l + 32 first exchange halves and add
+// their bit-sliced sums (l keeps replicas 0..31, l + 32 replicas 32..63), so each plane is one
+// 32 x 32 transpose per half.  All 64 lanes must take part (wave-uniform control flow).
+__device__ __forceinline__ void count_planes(const LaneCounter &n, int words, unsigned &acc)
+{
+  const int lane = (int)__lane_id();
+  uint32_t carry = 0;
+#pragma unroll
+  for (int k = 0; k <= LaneCounter::kPlanes; ++k) {
+    if (k > 0 && (words >> (k - 1)) == 0) break;   // twice `words` is below 2^k: planes k.. are zero
+    uint32_t s;
+    if (k < LaneCounter::kPlanes) {
+      const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)n.c[k], (uint32_t)(n.c[k] >> 32), false, false);
+      s = bit3<kTTXor3>(h[0], h[1], carry);
+      carry = bit3<kTTMaj>(h[0], h[1], carry);
+    } else {
+      s = carry;
+    }
+    s = transpose_stage<16>(s, lane);
+    s = transpose_stage<8>(s, lane);
+    s = transpose_stage<4>(s, lane);
+    s = transpose_stage<2>(s, lane);
+    s = transpose_stage<1>(s, lane);
+    acc += (unsigned)__popc(s) << k;
+  }
+}
+
+// Counts of the sites of one wave, its chunks of 64 starting at base, base + stride, ... (both
+// wave-uniform) and ending at N: n (acc[0]), n & n0 (acc[1]) and n0 & ~f (acc[2]) of the replica
+// whose bit this lane numbers, per word of the element, every array read once.
+template <int WPT>
+__device__ __forceinline__ void observe_sites(const u64 *n, const u64 *n0, const u64 *f, int N, int base, int stride,
+                                              unsigned (&acc)[3][WPT])
+{
+  const int lane = (int)__lane_id();
+  LaneCounter cnt[3][WPT];
+  int64_t at = base;
+  while (at < N) {
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+      for (int w = 0; w < WPT; ++w) cnt[o][w].clear();
+    int words = 0;
+    for (; at < N && words <= LaneCounter::kMaxWords - 4; at += (int64_t)4 * stride) {
+      Elem<WPT> x[4], x0[4], xf[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        words += at + (int64_t)q * stride < N;
+        const int64_t i = at + (int64_t)q * stride + lane;
+        if (i < N) {
+          x[q] = ld<WPT>(n, (int)i);
+          x0[q] = ld<WPT>(n0, (int)i);
+          xf[q] = ld<WPT>(f, (int)i);
+        } else {
+#pragma unroll
+          for (int w = 0; w < WPT; ++w) x[q].w[w] = x0[q].w[w] = xf[q].w[w] = 0;
+        }
+      }
+#pragma unroll
+      for (int w = 0; w < WPT; ++w) {
+        cnt[0][w].add4(x[0].w[w], x[1].w[w], x[2].w[w], x[3].w[w]);
+        cnt[1][w].add4(x[0].w[w] & x0[0].w[w], x[1].w[w] & x0[1].w[w], x[2].w[w] & x0[2].w[w], x[3].w[w] & x0[3].w[w]);
+        cnt[2][w].add4(x0[0].w[w] & ~xf[0].w[w], x0[1].w[w] & ~xf[1].w[w], x0[2].w[w] & ~xf[2].w[w],
+                       x0[3].w[w] & ~xf[3].w[w]);
+      }
+    }
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+      for (int w = 0; w < WPT; ++w) count_planes(cnt[o][w], words, acc[o][w]);
+  }
+}
+
 }  // namespace dev
 }  // namespace ka

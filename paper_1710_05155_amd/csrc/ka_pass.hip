@@ -1,6 +1,7 @@
 // ka_pass.hip -- global-memory class passes, observables and initial state (gfx950).
 //
 // Method: Boccagna, arXiv 1710.05155; the per-edge bit logic lives in ka_device.h.
+#include <algorithm>
 #include <mutex>
 
 #include "ka_device.h"
@@ -15,7 +16,10 @@ namespace {
 using namespace dev;
 
 constexpr int kPassBlock = 256;
-constexpr int kObsBlock = 256;
+constexpr int kObsBlock = 512;
+// Workgroups of one observation launch: at most two for each CU over all planes and states, at
+// most one for each CU of one plane, and about a third of the CUs before lanes take four sites
+constexpr int kObsBlocks = 512, kObsPlaneBlocks = 256, kObsSpread = 80;
 // Graph classes are uneven (greedy colouring): a class with fewer edges than this (over all
 // planes) runs in 64-thread workgroups, which spread it over more CUs; larger ones in
 // kPassBlock-thread workgroups.
@@ -84,13 +88,20 @@ __global__ __launch_bounds__(BLOCK) void k_pass_graph(PassGraph a, int m)
 
 // One launch counts a.rows states (blockIdx.z): the sim's own state, or snapshots taken by the
 // LDS-resident sweep loop.
+// Bound by reading n, n0 and f once (24 B per site-word).  The wave counts are added in LDS and
+// a workgroup makes one global add per count: with one per wave, the adds of all waves to the
+// same few lines took longer than the reads.
 template <int WPT>
 __global__ __launch_bounds__(kObsBlock) void k_observe(ObserveArgs a)
 {
+  __shared__ unsigned cnt[3 * 64 * WPT];
   const int plane = blockIdx.y;
   const int row = blockIdx.z;
+  const int tid = (int)threadIdx.x;
   const int lane = (int)__lane_id();
-  const int wave = (int)(blockIdx.x * (kObsBlock / 64) + threadIdx.x / 64);
+  for (int q = tid; q < 3 * 64 * WPT; q += kObsBlock) cnt[q] = 0;
+  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kObsBlock / 64) + tid / 64);
   const int nwaves = (int)(gridDim.x * (kObsBlock / 64));
   const size_t off = (size_t)plane * (size_t)a.N * WPT;
   const size_t soff = off + (size_t)row * a.row_stride;
@@ -99,32 +110,18 @@ __global__ __launch_bounds__(kObsBlock) void k_observe(ObserveArgs a)
   for (int o = 0; o < 3; ++o)
 #pragma unroll
     for (int w = 0; w < WPT; ++w) acc[o][w] = 0;
-  for (int base = wave * 64; base < a.N; base += nwaves * 64) {  // wave-uniform loop
-    const int idx = base + lane;
-    Elem<WPT> x, x0, xf;
-    if (idx < a.N) {
-      x = ld<WPT>(a.n + soff, idx);
-      x0 = ld<WPT>(a.n0 + off, idx);
-      xf = ld<WPT>(a.f + soff, idx);
-    } else {
-#pragma unroll
-      for (int w = 0; w < WPT; ++w) x.w[w] = x0.w[w] = xf.w[w] = 0;
-    }
-#pragma unroll
-    for (int w = 0; w < WPT; ++w) {
-      vertical_count(x.w[w], acc[0][w]);
-      vertical_count(x.w[w] & x0.w[w], acc[1][w]);
-      vertical_count(x0.w[w] & ~xf.w[w], acc[2][w]);
-    }
-  }
-  unsigned long long *out = a.out + (size_t)row * 3u * (size_t)a.R;
+  observe_sites<WPT>(a.n + soff, a.n0 + off, a.f + soff, a.N, wave * 64, nwaves * 64, acc);
 #pragma unroll
   for (int o = 0; o < 3; ++o)
 #pragma unroll
     for (int w = 0; w < WPT; ++w)
-      if (acc[o][w])
-        atomicAdd(&out[(size_t)o * a.R + (size_t)(plane * WPT + w) * 64 + lane],
-                  (unsigned long long)acc[o][w]);
+      if (acc[o][w]) atomicAdd(&cnt[(o * WPT + w) * 64 + lane], acc[o][w]);
+  __syncthreads();
+  unsigned long long *out = a.out + (size_t)row * 3u * (size_t)a.R;
+  for (int q = tid; q < 3 * 64 * WPT; q += kObsBlock) {
+    const int o = q / (64 * WPT), b = q - o * (64 * WPT);
+    if (cnt[q]) atomicAdd(&out[(size_t)o * a.R + (size_t)plane * (64 * WPT) + b], (unsigned long long)cnt[q]);
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -470,8 +467,14 @@ hipError_t launch_fill_u64(unsigned long long *p, int n, unsigned long long v, h
 hipError_t launch_observe(const ObserveArgs &a, int wpt, hipStream_t s)
 {
   if (a.rows < 1 || a.rows > 65535) return hipErrorInvalidValue;
-  int bx = (a.N + kObsBlock - 1) / kObsBlock;
-  if (bx > 512) bx = 512;
+  // Four sites per lane (one counter step), fewer only while that leaves most CUs idle, and at
+  // most kObsPlaneBlocks workgroups for one plane of one state: all of them add into the same
+  // 192 counts per word.  One state of 2^18 sites takes 7.2 us in 128 workgroups and 15.5 us in
+  // 512; 10 states of 4096 sites take 6.9 us in 2 workgroups each and 6.1 us in 8 each.
+  const int chunks = (a.N + kObsBlock - 1) / kObsBlock;
+  const int sets = (int)std::min<int64_t>((int64_t)a.planes * a.rows, kObsBlocks);   // planes x states
+  const int spread = std::max((chunks + 3) / 4, std::min(chunks, kObsSpread / sets));
+  const int bx = std::max(1, std::min(spread, std::min(kObsPlaneBlocks, kObsBlocks / sets)));
   const dim3 grid((unsigned)bx, (unsigned)a.planes, (unsigned)a.rows);
   if (wpt == 2)
     hipLaunchKernelGGL((k_observe<2>), grid, dim3(kObsBlock), 0, s, a);
