@@ -56,10 +56,11 @@ __device__ __forceinline__ u64 bit3(u64 a, u64 b, u64 c)
 // seed, so they stay in scalar registers; each round is two 32x32->64 multiplies and two
 // three-way xors.
 // ------------------------------------------------------------------------------------
-__device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1)
+template <int FIRST>   // rounds FIRST .. 9; k0, k1 are round FIRST's keys
+__device__ __forceinline__ uint4 philox_rounds(uint4 c, uint32_t k0, uint32_t k1)
 {
 #pragma unroll
-  for (int r = 0; r < 10; ++r) {
+  for (int r = FIRST; r < 10; ++r) {
     const u64 p0 = (u64)0xD2511F53u * (u64)c.x;
     const u64 p1 = (u64)0xCD9E8D57u * (u64)c.z;
     uint4 y;
@@ -73,6 +74,8 @@ __device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1)
   }
   return c;
 }
+
+__device__ __forceinline__ uint4 philox10(uint4 c, uint32_t k0, uint32_t k1) { return philox_rounds<0>(c, k0, k1); }
 
 __device__ __forceinline__ u64 lo_half(uint4 o) { return (u64)o.x | ((u64)o.y << 32); }
 __device__ __forceinline__ u64 hi_half(uint4 o) { return (u64)o.z | ((u64)o.w << 32); }

@@ -1160,8 +1160,7 @@ extern "C" int ka_init_k(const ka_graph *g, int m, int64_t K, uint64_t seed, int
     a.is_lattice = s->lattice;
     a.g = s->geom;
     a.site_of = s->site_of;
-    e = hipMemsetAsync(s->err, 0, sizeof(int), s->stream);
-    if (e == hipSuccess) e = ka::launch_init(a, s->R, s->wpt, s->stream);
+    e = ka::launch_init(a, s->R, s->wpt, s->stream);
     if (e != hipSuccess) {
       free_device(s);
       if (s->own_stream) (void)hipStreamDestroy(s->stream);

@@ -126,6 +126,12 @@ struct InitArgs {
   int is_lattice;
   LatticeGeom g;
   const int32_t *site_of;   // general graphs: canonical vertex of each device index
+  // selection among the keys near the threshold (set by launch_init): keys whose high 32 bits
+  // are below `lo` are occupied, those in [lo, lo + width) are candidates; at most `cap`
+  // candidates per replica are kept.  bin_mul = floor(kBins 2^32 / width).
+  uint32_t lo, width;
+  u64 bin_mul;
+  int cap;
 };
 
 struct ObserveArgs {

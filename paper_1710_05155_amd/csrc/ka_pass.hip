@@ -1,4 +1,4 @@
-// ka_pass.hip -- global-memory class passes, observables and initial state (gfx950).
+// ka_pass.hip -- global-memory class passes and observables (gfx950).
 //
 // Method: Boccagna, arXiv 1710.05155; the per-edge bit logic lives in ka_device.h.
 #include <algorithm>
@@ -124,226 +124,6 @@ __global__ __launch_bounds__(kObsBlock) void k_observe(ObserveArgs a)
   }
 }
 
-// ------------------------------------------------------------------------------------
-// LDS-resident sweep loop: one workgroup owns one plane of a small instance, keeps n and f
-// in LDS across all class passes of all requested sweeps (a barrier between passes) and
-// records observations in place; only the first load and the final store touch HBM.
-// ------------------------------------------------------------------------------------
-// ------------------------------------------------------------------------------------
-// Initial state (uniform K-subset per replica by smallest Philox keys).
-// k_init_select: one workgroup per replica pair (2h, 2h+1), which share Philox calls.
-// Radix selection of the K-th smallest key (u, i): 12-bit digits of u, most significant
-// first, histogrammed in LDS among keys that match the digits fixed so far, until the
-// bin that holds the K-th key has at most kCap keys; those are collected and ranked
-// exactly by (u, i).  Output: threshold (u*, i*) per replica; site i is occupied iff
-// (u_i, i) <= (u*, i*).
-// ------------------------------------------------------------------------------------
-constexpr int kSelBlock = 1024;
-constexpr int kDig = 12;
-constexpr int kBins = 1 << kDig;
-constexpr int kCap = 2048;
-
-constexpr int kBinsPerThread = kBins / kSelBlock;
-
-__device__ __forceinline__ bool key_matches(u64 u, u64 prefix, int pbits)
-{
-  return pbits == 0 || (u >> (64 - pbits)) == prefix;
-}
-
-// Exclusive prefix sum of v over the kSelBlock threads of the block (every thread calls it;
-// tmp holds one value per wave).  Counts stay below 2^32: at most N <= 2^31 keys.
-__device__ __forceinline__ unsigned block_exclusive_scan(unsigned v, unsigned *tmp)
-{
-  const int lane = (int)__lane_id();
-  const int wave = (int)threadIdx.x / 64;
-  unsigned x = v;   // inclusive scan within the wave
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned y = __shfl_up(x, d);
-    if (lane >= d) x += y;
-  }
-  if (lane == 63) tmp[wave] = x;
-  __syncthreads();
-  unsigned off = 0;
-  for (int w = 0; w < wave; ++w) off += tmp[w];
-  return off + x - v;
-}
-
-__global__ __launch_bounds__(kSelBlock) void k_init_select(InitArgs a)
-{
-  __shared__ unsigned hist[2][kBins];
-  __shared__ u64 cand_u[2][kCap];
-  __shared__ int cand_i[2][kCap];
-  __shared__ u64 prefix[2];
-  __shared__ int pbits[2];
-  __shared__ long long need[2];
-  __shared__ int done[2];
-  __shared__ int ncand[2];
-  __shared__ int sel_beta[2];
-  __shared__ unsigned sel_cum[2];
-  __shared__ unsigned scan_tmp[kSelBlock / 64];
-  const int hp = blockIdx.x;
-  const int tid = (int)threadIdx.x;
-  if (a.K == 0) {
-    if (tid < 2) {
-      a.thr_u[2 * hp + tid] = 0;
-      a.thr_i[2 * hp + tid] = -1;
-    }
-    return;
-  }
-  if (tid < 2) {
-    prefix[tid] = 0;
-    pbits[tid] = 0;
-    need[tid] = a.K;
-    done[tid] = a.N <= kCap;
-    ncand[tid] = 0;
-  }
-  __syncthreads();
-  while (!(done[0] && done[1])) {
-    for (int q = tid; q < 2 * kBins; q += kSelBlock) (&hist[0][0])[q] = 0;
-    __syncthreads();
-    for (int i = tid; i < a.N; i += kSelBlock) {
-      const uint4 o = philox10(make_uint4(0u, 0xFFFFFFFFu, (uint32_t)i, (uint32_t)hp), a.key0, a.key1);
-      const u64 uk[2] = {lo_half(o), hi_half(o)};
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        if (done[h]) continue;
-        const int pb = pbits[h];
-        if (!key_matches(uk[h], prefix[h], pb)) continue;
-        const int dig = (64 - pb) < kDig ? (64 - pb) : kDig;
-        const unsigned digit = (unsigned)((uk[h] >> (64 - pb - dig)) & ((1ull << dig) - 1ull));
-        atomicAdd(&hist[h][digit], 1u);
-      }
-    }
-    // The bin holding the need-th key: the one bin b with E[b] < need <= E[b] + hist[b],
-    // E the exclusive prefix sum of the histogram, found by a block-wide scan (thread t owns
-    // bins kBinsPerThread * t ...).  The scan's own barrier orders these initial values
-    // before the one thread that finds the bin writes it.
-    if (tid < 2) {
-      sel_beta[tid] = -1;
-      sel_cum[tid] = 0;
-    }
-    __syncthreads();   // the histogram is complete
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (done[h]) continue;   // block-uniform
-      unsigned c[kBinsPerThread];
-      unsigned sum = 0;
-#pragma unroll
-      for (int q = 0; q < kBinsPerThread; ++q) {
-        c[q] = hist[h][kBinsPerThread * tid + q];
-        sum += c[q];
-      }
-      const unsigned before = block_exclusive_scan(sum, scan_tmp);
-      unsigned e = before;
-#pragma unroll
-      for (int q = 0; q < kBinsPerThread; ++q) {
-        if ((long long)e < need[h] && need[h] <= (long long)e + (long long)c[q]) {
-          sel_beta[h] = kBinsPerThread * tid + q;
-          sel_cum[h] = e;
-        }
-        e += c[q];
-      }
-      __syncthreads();   // scan_tmp is reused by the next h
-    }
-    __syncthreads();
-    if (tid < 2 && !done[tid]) {
-      const int h = tid;
-      const int pb = pbits[h];
-      const int dig = (64 - pb) < kDig ? (64 - pb) : kDig;
-      int beta = sel_beta[h];
-      long long cum = sel_cum[h];
-      if (beta < 0 || beta >= (1 << dig)) {  // unreachable: need <= keys under the prefix
-        beta = (1 << dig) - 1;
-        cum = 0;
-        atomicOr(a.err, 2);
-      }
-      need[h] -= cum;
-      prefix[h] = (prefix[h] << dig) | (u64)beta;
-      pbits[h] = pb + dig;
-      done[h] = (hist[h][beta] <= (unsigned)kCap) || pbits[h] == 64;
-    }
-    __syncthreads();
-  }
-  for (int i = tid; i < a.N; i += kSelBlock) {
-    const uint4 o = philox10(make_uint4(0u, 0xFFFFFFFFu, (uint32_t)i, (uint32_t)hp), a.key0, a.key1);
-    const u64 uk[2] = {lo_half(o), hi_half(o)};
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if (!key_matches(uk[h], prefix[h], pbits[h])) continue;
-      const int slot = atomicAdd(&ncand[h], 1);
-      if (slot < kCap) {
-        cand_u[h][slot] = uk[h];
-        cand_i[h][slot] = i;
-      }
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int nc = ncand[h] < kCap ? ncand[h] : kCap;
-    if (ncand[h] > kCap) {
-      if (tid == 0) atomicOr(a.err, 1);
-      continue;
-    }
-    for (int s = tid; s < nc; s += kSelBlock) {
-      const u64 us = cand_u[h][s];
-      const int is = cand_i[h][s];
-      int rank = 0;
-      for (int q = 0; q < nc; ++q) {
-        const u64 uq = cand_u[h][q];
-        rank += (uq < us) || (uq == us && cand_i[h][q] < is);
-      }
-      if (rank == need[h] - 1) {
-        a.thr_u[2 * hp + h] = us;
-        a.thr_i[2 * hp + h] = is;
-      }
-    }
-  }
-}
-
-// Element index -> canonical site id.
-__device__ __forceinline__ int element_site(const InitArgs &a, int idx)
-{
-  if (!a.is_lattice) return a.site_of[idx];
-  const int sub = idx / a.g.P;
-  const int pos = idx - sub * a.g.P;
-  const Site s = decode(a.g, a.g.d, sub, pos);
-  return canonical(a.g, a.g.d, s);
-}
-
-template <int WPT>
-__global__ __launch_bounds__(256) void k_init_fill(InitArgs a)
-{
-  const int plane = blockIdx.y;
-  const size_t off = (size_t)plane * (size_t)a.N * WPT;
-  for (int idx = blockIdx.x * 256 + (int)threadIdx.x; idx < a.N; idx += gridDim.x * 256) {
-    const int i = element_site(a, idx);
-    Elem<WPT> x, z;
-#pragma unroll
-    for (int w = 0; w < WPT; ++w) {
-      const int word = plane * WPT + w;
-      u64 bits = 0;
-      for (int l = 0; l < 64; l += 2) {
-        const int b = word * 64 + l;
-        const uint4 o = philox10(make_uint4(0u, 0xFFFFFFFFu, (uint32_t)i, (uint32_t)(b >> 1)),
-                                 a.key0, a.key1);
-        const u64 u0 = lo_half(o), u1 = hi_half(o);
-        const u64 t0 = a.thr_u[b], t1 = a.thr_u[b + 1];
-        const long long i0 = a.thr_i[b], i1 = a.thr_i[b + 1];
-        const bool in0 = (u0 < t0) || (u0 == t0 && (long long)i <= i0);
-        const bool in1 = (u1 < t1) || (u1 == t1 && (long long)i <= i1);
-        bits |= ((u64)in0 << l) | ((u64)in1 << (l + 1));
-      }
-      x.w[w] = bits;
-      z.w[w] = 0;
-    }
-    st<WPT>(a.n + off, idx, x);
-    st<WPT>(a.n0 + off, idx, x);
-    st<WPT>(a.f + off, idx, z);
-  }
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------------------------
@@ -399,21 +179,6 @@ hipError_t launch_pass_graph(const PassGraph &args, int z, int m, int wpt, hipSt
     default: return hipErrorInvalidValue;
   }
 #undef KA_GR
-  return hipGetLastError();
-}
-
-hipError_t launch_init(const InitArgs &a, int R, int wpt, hipStream_t s)
-{
-  hipLaunchKernelGGL(k_init_select, dim3((unsigned)(R / 2)), dim3(kSelBlock), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int planes = (R / 64) / wpt;
-  int bx = (a.N + 255) / 256;
-  if (bx > 4096) bx = 4096;
-  if (wpt == 2)
-    hipLaunchKernelGGL((k_init_fill<2>), dim3((unsigned)bx, (unsigned)planes), dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_init_fill<1>), dim3((unsigned)bx, (unsigned)planes), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
