@@ -106,7 +106,10 @@ void ka_graph_free(ka_graph *g);
  * that its LDS-resident sweeps generate ahead (at most 8 MiB, allocated on the first such
  * sweep; a layout whose words for a single sweep would exceed 8 MiB draws them in the loop
  * instead), and the state snapshots its ka_run observations are counted from (at most
- * 4 MiB, allocated by the first ka_run that takes them). */
+ * 4 MiB, allocated by the first ka_run that takes them).  For a larger 2D lattice it includes the
+ * same words (at most 8 MiB) and, above L = 88, a second copy of n, which its first sweep
+ * allocates; a sim that only a batch or a server sweeps takes neither, and the server does not
+ * count them. */
 int ka_footprint(const ka_graph *g, int n_replicas, size_t *device_bytes);
 
 /* Create a simulation of n_replicas (a positive multiple of 64) independent replicas on the
@@ -194,6 +197,11 @@ int ka_sim_info(const ka_sim *s, int64_t *N, int *n_replicas, int64_t *K, int *m
  *   KA_OPT_PATH:   0 = automatic, 1 = one kernel per class pass over global memory,
  *                  2 = whole sweep loop inside one workgroup per word plane with the plane in
  *                      LDS (only if it fits; KA_EINVAL otherwise).  Results are identical.
+ *                  Paths 0 and 2 run 2D lattices on 4 x 4 blocks of sites held in registers:
+ *                  the whole loop in one workgroup per word up to L = 88, above that one to
+ *                  three sweeps a launch on tiles of the lattice (class passes while
+ *                  KA_OPT_TIMING, KA_OPT_PLANE_STREAMS or KA_OPT_PLANE_GROUPS is set and the word
+ *                  plane does not fit in LDS, and under stream capture).
  *   KA_OPT_TIMING: k > 0 brackets every k-th class-pass launch with HIP events on the sim's
  *                  stream (for per-kernel durations, read with ka_timing); 0 = off.
  *   KA_OPT_NOISE:  0 (default) = an independent acceptance bit per replica, edge and sweep;
@@ -237,11 +245,13 @@ int ka_set_option(ka_sim *s, int option, int64_t value);
 
 /* Class-pass kernel launches so far (one per class step, or one per word plane and class
  * step when the planes run on their own streams, or one per group of planes and class step
- * when they run group by group; a merged run of tiny graph classes counts once), and among them the number bracketed by
+ * when they run group by group; a merged run of tiny graph classes counts once, and so does a
+ * launch over the tiles of a 2D lattice), and among them the number bracketed by
  * events and their summed duration in milliseconds (synchronises the stream). */
 int ka_timing(ka_sim *s, int64_t *launches, int64_t *timed, double *timed_ms);
 
-/* Path a ka_sweep would take now: 1 = global class passes, 2 = LDS-resident. */
+/* Path a ka_sweep would take now: 2 = resident in one workgroup (the word plane fits in LDS and
+ * KA_OPT_PATH is not 1), 1 = otherwise. */
 int ka_sim_path(const ka_sim *s, int *path);
 
 /* Release a sim.  If the sim is still a batch member, its batch is first run to completion

@@ -514,6 +514,8 @@ void free_device(ka_sim *s)
   (void)hipFree(s->lds_snap);
   s->lds_snap = nullptr;
   s->lds_snap_rows = 0;
+  (void)hipFree(s->n_next);
+  s->n_next = nullptr;
   s->n = s->n0 = s->f = nullptr;
 }
 
@@ -556,6 +558,33 @@ bool use_lds(const ka_sim *s)
   if (s->path_opt == 1) return false;
   if (s->path_opt == 2) return s->lds_fits;
   return s->lds_fits;
+}
+
+// How a ka_sweep of the sim runs.  All of them give the same results.
+enum class Route {
+  passes,     // one launch per class pass over global memory
+  lds,        // whole sweep loop with a word plane in one workgroup's LDS
+  resident,   // 2D: whole sweep loop with a word in one workgroup's registers and LDS
+  tiles       // 2D: one to three sweeps per launch, tiles in registers and LDS
+};
+
+bool capturing(const ka_sim *s)
+{
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(s->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+Route route(const ka_sim *s)
+{
+  if (!s->lattice || s->geom.d != 2) return use_lds(s) ? Route::lds : Route::passes;
+  if (s->path_opt == 1) return Route::passes;
+  const bool small = s->geom.P <= ka::kSquareResidentP;
+  // Options that arrange class passes keep them (they have no effect on a sim whose word plane
+  // fits in LDS).
+  if (!use_lds(s) && (s->plane_streams || s->plane_group_opt >= 0 || s->timing_every > 0)) return Route::passes;
+  // Nor can a capture allocate the second copy of n, or its replays swap the two.
+  if (capturing(s) && !(small && use_lds(s))) return Route::passes;
+  return small ? Route::resident : Route::tiles;
 }
 
 hipEvent_t pooled_event(ka_sim *s)
@@ -778,6 +807,21 @@ int64_t lds_acc_plan(int d, int L, int R, size_t *bytes)
   return sweeps;
 }
 
+// The same for a 2D lattice of P positions and W words (32 words per position, word and sweep).
+// 0 sweeps when one sweep's words exceed the budget: a resident sim then runs as class passes (at
+// 8 MiB its words alone occupy 64 CUs or more), and tiles draw in the sweep, since writing and reading the words
+// back would cost more than the draws of the tiles' overlap (L = 1024 x 64: 24.4 against 20.3
+// us per sweep; L = 512 x 256: 23.3 against 22.6).
+int64_t square_acc_plan(int P, int W, size_t *bytes)
+{
+  if (bytes) *bytes = 0;
+  const size_t per_sweep = (size_t)W * 256u * (size_t)P;
+  if (per_sweep > kLdsAccBudget) return 0;
+  const int64_t sweeps = std::min<int64_t>(8191, (int64_t)(kLdsAccBudget / per_sweep));
+  if (bytes) *bytes = (size_t)sweeps * per_sweep;
+  return sweeps;
+}
+
 // The same for the LDS graph sweep over E class-sorted edges of degree z whose largest class
 // has max_class edges; 0 sweeps if a class has more edges per thread than the sweep prefetches
 // or the layout draws its words in the loop.
@@ -809,8 +853,9 @@ int64_t lds_chunk(ka_sim *s)
   if (!s->lds_acc_tried) {
     s->lds_acc_tried = true;
     size_t bytes = 0;
-    const int64_t sweeps = s->lattice ? lds_acc_plan(s->geom.d, s->geom.L, s->R, &bytes)
-                                      : lds_acc_plan_graph((int64_t)s->edges_total,
+    const int64_t sweeps = s->lattice && s->geom.d == 2 ? square_acc_plan(s->geom.P, s->W, &bytes)
+                           : s->lattice                 ? lds_acc_plan(s->geom.d, s->geom.L, s->R, &bytes)
+                                                        : lds_acc_plan_graph((int64_t)s->edges_total,
                                                            max_class_edges(s->plan->class_start), s->z, s->R, &bytes);
     if (sweeps > 0 && dalloc(&s->lds_acc, bytes) == hipSuccess) {
       s->lds_acc_sweeps = sweeps;
@@ -939,9 +984,117 @@ hipError_t launch_lds(ka_sim *s, int64_t t_from, int64_t t_to, int q0, int q1, b
   return e;
 }
 
-hipError_t sweep_global(ka_sim *s, int64_t n)
+ka::SquareArgs square_args(const ka_sim *s, int64_t t0, int64_t sweeps)
 {
-  if (n <= 0) return hipSuccess;
+  ka::SquareArgs a{};
+  a.n = s->n;
+  a.f = s->f;
+  a.g = s->geom;
+  a.W = s->W;
+  a.wpt = s->wpt;
+  a.noise = s->noise;
+  a.t0 = (uint32_t)t0;
+  a.n_sweeps = (int)sweeps;
+  a.key0 = (uint32_t)s->seed;
+  a.key1 = (uint32_t)(s->seed >> 32);
+  a.acc = s->lds_acc;
+  return a;
+}
+
+// Resident 2D launch covering sweeps [t_from, t_to) (at most lds_chunk of them) that also takes
+// observations obs[q0..q1) as snapshots (at most lds_snap_rows) and counts them.
+hipError_t launch_resident(ka_sim *s, int64_t t_from, int64_t t_to, int q0, int q1)
+{
+  if (t_to == t_from) return observe_rows(s, s->n, s->f, 0, q0, q1 - q0);
+  ka::SquareArgs a = square_args(s, t_from, t_to - t_from);
+  hipError_t e = ka::launch_square_accept(a, s->stream);
+  a.obs_times = s->obs_d + q0;
+  a.n_obs = q1 - q0;
+  a.snap = s->lds_snap;
+  if (q1 > q0 && (!s->lds_snap || (size_t)(q1 - q0) > s->lds_snap_rows)) return hipErrorInvalidValue;
+  if (e == hipSuccess) e = ka::launch_square_resident(a, s->m, s->stream);
+  if (e == hipSuccess && q1 > q0) {
+    const size_t row_words = (size_t)s->N * (size_t)s->W;
+    e = observe_rows(s, s->lds_snap, s->lds_snap + row_words, 2u * row_words, q0, q1 - q0);
+  }
+  return e;
+}
+
+// n sweeps of a large 2D lattice, one to three a launch, between the two copies of n.
+hipError_t sweep_tiles(ka_sim *s, int64_t n)
+{
+  if (!s->n_next) {
+    const hipError_t e = dalloc(&s->n_next, (size_t)s->N * (size_t)s->W * 8u);
+    if (e != hipSuccess) return e;
+  }
+  const int64_t chunk = lds_chunk(s);
+  hipError_t e = hipSuccess;
+  for (int64_t done = 0; done < n && e == hipSuccess;) {
+    const int64_t k = std::min(chunk, n - done);
+    if (s->lds_acc) e = ka::launch_square_accept(square_args(s, s->t + done, k), s->stream);
+    for (int64_t q = 0; q < k && e == hipSuccess;) {
+      ka::SquareArgs a = square_args(s, s->lds_acc ? s->t + done : s->t + done + q, k);
+      a.sweep = (int)q;
+      a.n_out = s->n_next;
+      const int ns = (int)std::min<int64_t>(ka::square_sweeps_per_launch(a), k - q);
+      e = ka::launch_square_tile(a, ns, s->m, s->stream);
+      if (e != hipSuccess) break;
+      std::swap(s->n, s->n_next);
+      s->launches += 1;
+      q += ns;
+    }
+    done += k;
+  }
+  return e;
+}
+
+// The sim's route; a resident or tile sweep whose buffers cannot be allocated runs as class passes.
+Route sweep_route(ka_sim *s)
+{
+  const Route by = route(s);
+  if (by == Route::resident) {
+    (void)lds_chunk(s);
+    if (!s->lds_acc) return Route::passes;
+  }
+  if (by == Route::tiles && !s->n_next && dalloc(&s->n_next, (size_t)s->N * (size_t)s->W * 8u) != hipSuccess) {
+    (void)hipGetLastError();
+    s->n_next = nullptr;
+    return Route::passes;
+  }
+  return by;
+}
+
+// ka_run on the resident path: chunks [a, b) of at most lds_chunk sweeps and at most as many
+// observations as the snapshot buffer holds; those due where a chunk starts with no sweep before
+// them count the state itself.
+hipError_t run_resident(ka_sim *s, const int64_t *obs_times, int n_obs)
+{
+  hipError_t e = hipMemcpyAsync(s->obs_d, obs_times, (size_t)n_obs * sizeof(int64_t), hipMemcpyHostToDevice, s->stream);
+  const int64_t chunk = lds_chunk(s);
+  const size_t fit = kLdsSnapBudget / lds_snap_row_bytes(s->N, s->R);
+  const int rows = ensure_lds_snap(s, std::min<size_t>(fit, (size_t)n_obs)) ? (int)std::min<size_t>(fit, (size_t)n_obs) : 0;
+  int64_t a = s->t;
+  for (int q = 0; q < n_obs && e == hipSuccess;) {
+    int q1 = q;
+    while (q1 < n_obs && obs_times[q1] == a) ++q1;
+    const int64_t last = obs_times[n_obs - 1];
+    if (q1 > q && (rows == 0 || q1 - q >= rows || last == a)) {
+      e = launch_resident(s, a, a, q, q1);
+      q = q1;
+      continue;
+    }
+    int64_t b = std::min(a + chunk, rows > 0 ? last : obs_times[q]);
+    while (rows > 0 && q1 < n_obs && obs_times[q1] <= b && q1 - q < rows) ++q1;
+    if (rows > 0 && q1 < n_obs && obs_times[q1] <= b) b = obs_times[q1 - 1];   // the buffer is full there
+    e = launch_resident(s, a, b, q, q1);
+    q = q1;
+    a = b;
+  }
+  return e;
+}
+
+hipError_t sweep_passes(ka_sim *s, int64_t n)
+{
   const bool split = plane_split(s);
   hipError_t e = hipSuccess;
   if (split) {
@@ -975,6 +1128,13 @@ hipError_t sweep_global(ka_sim *s, int64_t n)
   return e;
 }
 
+// n sweeps that leave the state in global memory after each.
+hipError_t sweep_global(ka_sim *s, Route by, int64_t n)
+{
+  if (n <= 0) return hipSuccess;
+  return by == Route::tiles ? sweep_tiles(s, n) : sweep_passes(s, n);
+}
+
 hipError_t observe_global(ka_sim *s, int row) { return observe_rows(s, s->n, s->f, 0, row, 1); }
 
 // After a stream synchronisation: report a failure flagged by the initial-state kernels.
@@ -1000,30 +1160,51 @@ int check_sim(const ka_sim *s)
 
 }  // namespace
 
+// Device bytes of a sim that only a batch sweeps (it takes no buffers of its own for sweeps of a
+// large 2D lattice).
+int ka_sim_batch_bytes(const ka_graph *g, int n_replicas, size_t *device_bytes)
+{
+  if (!g || !device_bytes) return fail(KA_EINVAL, "NULL argument");
+  if (n_replicas <= 0 || n_replicas % 64 != 0) return fail(KA_EINVAL, "n_replicas must be a positive multiple of 64");
+  *device_bytes = state_bytes(g->N, n_replicas) + graph_device_bytes(g) +
+                  (size_t)n_replicas * 16u + (size_t)3 * n_replicas * 8u + 64u +
+                  (g->lattice ? 0 : fsat_bytes(g->N, n_replicas));
+  const int wpt = ((n_replicas / 64) % 2 == 0) ? 2 : 1;
+  if (ka::sweep_lds_bytes((int)g->N, wpt) + 4096 <= (size_t)ka::max_lds_bytes()) {
+    // an instance on the LDS-resident path adds its pre-generated acceptance words and its
+    // observation snapshots
+    size_t acc = 0;
+    if (g->lattice) {
+      (void)lds_acc_plan(g->d, g->L, n_replicas, &acc);
+    } else {
+      std::vector<int> cs((size_t)g->C + 1, 0);
+      for (int32_t c : g->ecls) cs[(size_t)c + 1] += 1;
+      for (size_t c = 1; c < cs.size(); ++c) cs[c] += cs[c - 1];
+      (void)lds_acc_plan_graph((int64_t)g->ecls.size(), max_class_edges(cs), g->z, n_replicas, &acc);
+    }
+    const size_t row = lds_snap_row_bytes(g->N, n_replicas);
+    *device_bytes += acc + (kLdsSnapBudget / row) * row;
+  }
+  return KA_OK;
+}
+
 extern "C" int ka_footprint(const ka_graph *g, int n_replicas, size_t *device_bytes)
 {
   return ka_guard([&]() -> int {
-    if (!g || !device_bytes) return fail(KA_EINVAL, "NULL argument");
-    if (n_replicas <= 0 || n_replicas % 64 != 0) return fail(KA_EINVAL, "n_replicas must be a positive multiple of 64");
-    *device_bytes = state_bytes(g->N, n_replicas) + graph_device_bytes(g) +
-                    (size_t)n_replicas * 16u + (size_t)3 * n_replicas * 8u + 64u +
-                    (g->lattice ? 0 : fsat_bytes(g->N, n_replicas));
+    const int rc = ka_sim_batch_bytes(g, n_replicas, device_bytes);
+    if (rc != KA_OK || !g->lattice || g->d != 2) return rc;
     const int wpt = ((n_replicas / 64) % 2 == 0) ? 2 : 1;
-    if (ka::sweep_lds_bytes((int)g->N, wpt) + 4096 <= (size_t)ka::max_lds_bytes()) {
-      // an instance on the LDS-resident path adds its pre-generated acceptance words and its
-      // observation snapshots
+    const bool fits = ka::sweep_lds_bytes((int)g->N, wpt) + 4096 <= (size_t)ka::max_lds_bytes();
+    const int64_t P = g->N / 16;
+    if (!fits) {
+      // words drawn ahead (those of a sim whose word plane fits in LDS are counted above) and, for
+      // a lattice in one workgroup, snapshots
       size_t acc = 0;
-      if (g->lattice) {
-        (void)lds_acc_plan(g->d, g->L, n_replicas, &acc);
-      } else {
-        std::vector<int> cs((size_t)g->C + 1, 0);
-        for (int32_t c : g->ecls) cs[(size_t)c + 1] += 1;
-        for (size_t c = 1; c < cs.size(); ++c) cs[c] += cs[c - 1];
-        (void)lds_acc_plan_graph((int64_t)g->ecls.size(), max_class_edges(cs), g->z, n_replicas, &acc);
-      }
+      (void)square_acc_plan((int)P, n_replicas / 64, &acc);
       const size_t row = lds_snap_row_bytes(g->N, n_replicas);
-      *device_bytes += acc + (kLdsSnapBudget / row) * row;
+      *device_bytes += acc + (P <= ka::kSquareResidentP ? (kLdsSnapBudget / row) * row : 0);
     }
+    if (P > ka::kSquareResidentP) *device_bytes += (size_t)g->N * (size_t)(n_replicas / 64) * 8u;   // second copy of n
     return KA_OK;
   });
 }
@@ -1192,16 +1373,21 @@ extern "C" int ka_sweep(ka_sim *s, int64_t n_sweeps)
     if (s->t + n_sweeps >= (1ll << 32)) return fail(KA_ESTATE, "sweep index would reach 2^32");
     DeviceGuard dg(s->device);
     hipError_t e = hipSuccess;
-    if (use_lds(s)) {
+    const Route by = sweep_route(s);
+    if (by == Route::resident || by == Route::lds) {
       int64_t done = 0;
       while (done < n_sweeps && e == hipSuccess) {
         const int64_t chunk = std::min(lds_chunk(s), n_sweeps - done);
-        e = ensure_obs_buffers(s, 1);
-        if (e == hipSuccess) e = launch_lds(s, s->t + done, s->t + done + chunk, 0, 0, false);
+        if (by == Route::resident) {
+          e = launch_resident(s, s->t + done, s->t + done + chunk, 0, 0);
+        } else {
+          e = ensure_obs_buffers(s, 1);
+          if (e == hipSuccess) e = launch_lds(s, s->t + done, s->t + done + chunk, 0, 0, false);
+        }
         done += chunk;
       }
     } else {
-      e = sweep_global(s, n_sweeps);
+      e = sweep_global(s, by, n_sweeps);
     }
     if (e != hipSuccess) return hip_fail(e, "ka_sweep");
     s->t += n_sweeps;
@@ -1228,7 +1414,10 @@ extern "C" int ka_run(ka_sim *s, const int64_t *obs_times, int n_obs, int64_t *d
     if (e != hipSuccess) return fail(KA_ENOMEM, "observation buffers: %s", hipGetErrorString(e));
     const size_t cbytes = (size_t)n_obs * 3u * (size_t)s->R * sizeof(unsigned long long);
     e = hipMemsetAsync(s->counts, 0, cbytes, s->stream);
-    if (e == hipSuccess && use_lds(s)) {
+    const Route by = sweep_route(s);
+    if (e == hipSuccess && by == Route::resident) {
+      e = run_resident(s, obs_times, n_obs);
+    } else if (e == hipSuccess && by == Route::lds) {
       e = hipMemcpyAsync(s->obs_d, obs_times, (size_t)n_obs * sizeof(int64_t), hipMemcpyHostToDevice, s->stream);
       // chunks [a, b) of at most lds_chunk sweeps; observation q goes to the first chunk
       // that can record it (times in [a, b] for the first chunk, (a, b] afterwards)
@@ -1256,7 +1445,7 @@ extern "C" int ka_run(ka_sim *s, const int64_t *obs_times, int n_obs, int64_t *d
     } else {
       for (int q = 0; q < n_obs && e == hipSuccess; ++q) {
         const int64_t n = obs_times[q] - s->t;
-        e = sweep_global(s, n);
+        e = sweep_global(s, by, n);
         s->t = obs_times[q];
         if (e == hipSuccess) e = observe_global(s, q);
       }

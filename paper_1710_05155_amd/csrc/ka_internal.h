@@ -111,6 +111,29 @@ struct SweepLds {
   u64 *snap;
 };
 
+// 2D lattices, one word at a time (ka_square.hip).
+struct SquareArgs {
+  u64 *n;
+  u64 *f;
+  u64 *n_out;                // tiles: the next sweep's n
+  LatticeGeom g;
+  int W, wpt;                // words of the sim, words per element of its layout
+  int noise;                 // 0: acceptance bit per replica, 1: shared by all replicas
+  uint32_t t0, key0, key1;
+  u64 *acc;                  // acceptance words drawn ahead (tiles: null = drawn in the sweep)
+  int n_sweeps;              // sweeps that acc holds, from t0 (resident: all of them run)
+  int sweep;                 // tiles: the first of them that this launch runs
+  const int64_t *obs_times;  // resident: observations as snapshots (layout of SweepLds::snap)
+  int n_obs;
+  u64 *snap;
+};
+// Positions (4 x 4 blocks) of a lattice that one workgroup holds.
+constexpr int kSquareResidentP = 512;
+hipError_t launch_square_accept(const SquareArgs &a, hipStream_t s);
+hipError_t launch_square_resident(const SquareArgs &a, int m, hipStream_t s);
+int square_sweeps_per_launch(const SquareArgs &a);
+hipError_t launch_square_tile(const SquareArgs &a, int sweeps, int m, hipStream_t s);
+
 struct InitArgs {
   int N;
   int64_t K;

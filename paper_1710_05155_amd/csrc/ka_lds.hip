@@ -387,13 +387,8 @@ hipError_t launch_lds_accept(const SweepLds &a, bool lattice, int wpt, hipStream
     return hipErrorInvalidValue;
   const dim3 grid((unsigned)(a.n_sweeps * a.C), (unsigned)planes);
   const dim3 block(kLdsBlock);
-  if (a.g.d == 2) {
-    if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_lattice<2, 2>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_lds_accept_lattice<2, 1>), grid, block, 0, s, a);
-  } else {
-    if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_lattice<3, 2>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_lds_accept_lattice<3, 1>), grid, block, 0, s, a);
-  }
+  if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_lattice<3, 2>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_lds_accept_lattice<3, 1>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -428,28 +423,20 @@ hipError_t launch_sweep_lds(const SweepLds &a, bool lattice, int zdeg, int m, in
   do {                                                                            \
     if (a.acc) KA_LDS_G1(Z, W, true); else KA_LDS_G1(Z, W, false);                 \
   } while (0)
-  if (lattice && (a.g.d == 2 ? 4 : 16) * a.g.P > kLdsSlots * kLdsBlock) return hipErrorInvalidValue;
+  if (lattice && (a.g.d != 3 || 16 * a.g.P > kLdsSlots * kLdsBlock)) return hipErrorInvalidValue;
   if (lattice) {
     if (a.acc && !lds_accept_supported(a.g.d, wpt, lds_lattice_slots(a.g.d, a.g.P))) return hipErrorInvalidValue;
     const bool g = a.acc != nullptr;
-    if (a.g.d == 2) {
-      if (wpt == 2) {
-        if (g) KA_LDS_L(2, 2, true); else KA_LDS_L(2, 2, false);
+    if (wpt == 2) {
+      if (g) {
+        e = set_lds(k_sweep_lds_lattice<3, 2, true, 1>, lds_bytes);
+        if (e == hipSuccess)
+          hipLaunchKernelGGL((k_sweep_lds_lattice<3, 2, true, 1>), grid, block, lds_bytes, s, a, m);
       } else {
-        if (g) KA_LDS_L(2, 1, true); else KA_LDS_L(2, 1, false);
+        KA_LDS_L(3, 2, false);
       }
-    } else {
-      if (wpt == 2) {
-        if (g) {
-          e = set_lds(k_sweep_lds_lattice<3, 2, true, 1>, lds_bytes);
-          if (e == hipSuccess)
-            hipLaunchKernelGGL((k_sweep_lds_lattice<3, 2, true, 1>), grid, block, lds_bytes, s, a, m);
-        } else {
-          KA_LDS_L(3, 2, false);
-        }
-      } else if (g) KA_LDS_L(3, 1, true);
-      else KA_LDS_L(3, 1, false);
-    }
+    } else if (g) KA_LDS_L(3, 1, true);
+    else KA_LDS_L(3, 1, false);
   } else {
     if (a.acc && (a.acc_slots < 1 || a.acc_slots > kLdsGraphAcceptSlots || !lds_graph_accept_supported(zdeg, wpt)))
       return hipErrorInvalidValue;

@@ -66,6 +66,7 @@ struct ka_sim {
   hipEvent_t join_ev[2] = {nullptr, nullptr};
   // device memory
   ka::u64 *n = nullptr, *n0 = nullptr, *f = nullptr;
+  ka::u64 *n_next = nullptr;          // large 2D lattices: second copy of n, swapped with n by each sweep
   int32_t *nbr = nullptr;             // graphs: [2(z-1)][E] neighbour lists of the records
   size_t edges_total = 0;             // graphs: E
   int4 *edges = nullptr;
@@ -118,6 +119,9 @@ int ka_sim_steps_per_sweep(const ka_sim *s);
 // planes in the sim's groups as ka_sweep runs them (each group through all `count` launches
 // before the next); s->t is left as it is.  A batch runs its one-at-a-time members with it.
 hipError_t ka_sim_passes(ka_sim *s, int64_t p0, int64_t count, hipStream_t stream);
+// Device bytes of a sim that only a batch sweeps: ka_footprint without the buffers that its own
+// sweeps of a large 2D lattice take.
+int ka_sim_batch_bytes(const ka_graph *g, int n_replicas, size_t *device_bytes);
 // Counts of ka_observe enqueued on the sim's stream into pinned host memory (3 * R values).
 int ka_sim_observe_async(ka_sim *s, unsigned long long *host_out);
 // Move a sim onto a new stream that it owns (its old stream may then be destroyed).  With

@@ -399,7 +399,7 @@ extern "C" int ka_server_submit(ka_server *sv, const ka_job_desc *job, int64_t *
     } else {
       j->obs.push_back(job->n_sweeps);
     }
-    if (ka_footprint(job->graph, job->n_replicas, &j->footprint) != KA_OK) return KA_EINVAL;
+    if (ka_sim_batch_bytes(job->graph, job->n_replicas, &j->footprint) != KA_OK) return KA_EINVAL;
     j->footprint += j->obs.size() * 3u * (size_t)job->n_replicas * 8u;
     if (j->footprint > sv->budget) return sfail(KA_EINVAL, "job needs %zu device bytes, budget is %zu", j->footprint, sv->budget);
     j->attempts = (double)N * (double)job->n_replicas * (double)job->n_sweeps;
