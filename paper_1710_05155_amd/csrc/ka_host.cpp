@@ -564,7 +564,7 @@ bool use_lds(const ka_sim *s)
 enum class Route {
   passes,     // one launch per class pass over global memory
   lds,        // whole sweep loop with a word plane in one workgroup's LDS
-  resident,   // 2D: whole sweep loop with a word in one workgroup's registers and LDS
+  resident,   // lattices: whole sweep loop with a word in one workgroup's registers and LDS
   tiles       // 2D: one to three sweeps per launch, tiles in registers and LDS
 };
 
@@ -574,15 +574,19 @@ bool capturing(const ka_sim *s)
   return hipStreamIsCapturing(s->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
 }
 
+// A lattice that one workgroup per word holds on register blocks.
+bool block_resident(int d, int64_t P) { return P <= (d == 2 ? ka::kSquareResidentP : ka::kCubeResidentP); }
+
 Route route(const ka_sim *s)
 {
-  if (!s->lattice || s->geom.d != 2) return use_lds(s) ? Route::lds : Route::passes;
-  if (s->path_opt == 1) return Route::passes;
-  const bool small = s->geom.P <= ka::kSquareResidentP;
+  if (!s->lattice) return use_lds(s) ? Route::lds : Route::passes;
+  const bool small = block_resident(s->geom.d, s->geom.P);
+  if (s->path_opt == 1 || (s->geom.d == 3 && !small)) return Route::passes;
   // Options that arrange class passes keep them (they have no effect on a sim whose word plane
   // fits in LDS).
   if (!use_lds(s) && (s->plane_streams || s->plane_group_opt >= 0 || s->timing_every > 0)) return Route::passes;
-  // Nor can a capture allocate the second copy of n, or its replays swap the two.
+  if (s->geom.d == 3 && s->geom.P < ka::kCubeMinP) return Route::lds;
+  // A capture cannot allocate, nor can its replays swap the two copies of n.
   if (capturing(s) && !(small && use_lds(s))) return Route::passes;
   return small ? Route::resident : Route::tiles;
 }
@@ -789,35 +793,20 @@ constexpr size_t kLdsAccBudget = (size_t)8 << 20;  // bytes of pre-generated acc
 // launch's one workgroup counts them in place.
 constexpr size_t kLdsSnapBudget = (size_t)4 << 20;
 
-// Sweeps per launch and buffer bytes of the pre-generated acceptance words of an LDS lattice
-// sweep (d, L, R); 0 sweeps if that layout draws its words in the loop.
-int64_t lds_acc_plan(int d, int L, int R, size_t *bytes)
-{
-  const int wpt = ((R / 64) % 2 == 0) ? 2 : 1;
-  const int planes = (R / 64) / wpt;
-  if (bytes) *bytes = 0;
-  const int Q = L / 4;
-  const int P = d == 2 ? Q * Q : Q * Q * Q;
-  if (!ka::lds_accept_supported(d, wpt, ka::lds_lattice_slots(d, P))) return 0;
-  const size_t per_sweep = (size_t)planes * (size_t)(4 * d) * (size_t)ka::lds_lattice_slots(d, P) * 1024u *
-                           (size_t)wpt * 8u;
-  if (per_sweep > kLdsAccBudget) return 0;   // drawn in the loop: the buffer stays within budget
-  const int64_t sweeps = std::max<int64_t>(1, std::min<int64_t>(kLdsChunk, (int64_t)(kLdsAccBudget / per_sweep)));
-  if (bytes) *bytes = (size_t)sweeps * per_sweep;
-  return sweeps;
-}
-
-// The same for a 2D lattice of P positions and W words (32 words per position, word and sweep).
-// 0 sweeps when one sweep's words exceed the budget: a resident sim then runs as class passes (at
-// 8 MiB its words alone occupy 64 CUs or more), and tiles draw in the sweep, since writing and reading the words
-// back would cost more than the draws of the tiles' overlap (L = 1024 x 64: 24.4 against 20.3
-// us per sweep; L = 512 x 256: 23.3 against 22.6).
-int64_t square_acc_plan(int P, int W, size_t *bytes)
+// Sweeps per launch and buffer bytes of the acceptance words drawn ahead for a lattice that does not
+// run as class passes (P positions, W words); 0 sweeps if they are drawn in the sweep.  Per word,
+// position and sweep they are 32 words in 2D and 192 in 3D.  One sweep's words above 8 MiB are not
+// worth writing and reading back: tiles (whose overlap draws some words twice) take 24.4 us per
+// sweep of L = 1024 x 64 replicas with them and 20.3 without, L = 64 x 16384 20.5 and 12.9.
+int64_t block_acc_plan(int d, int64_t P, int W, size_t *bytes)
 {
   if (bytes) *bytes = 0;
-  const size_t per_sweep = (size_t)W * 256u * (size_t)P;
-  if (per_sweep > kLdsAccBudget) return 0;
-  const int64_t sweeps = std::min<int64_t>(8191, (int64_t)(kLdsAccBudget / per_sweep));
+  const size_t per_sweep = (size_t)(d == 2 ? 256 : 1536) * (size_t)P * (size_t)W;
+  if (per_sweep > kLdsAccBudget || (d == 3 && !block_resident(d, P))) return 0;
+  const int64_t sweeps = std::min<int64_t>(5461, (int64_t)(kLdsAccBudget / per_sweep));   // grid limit of the draws
+  // two launches for one or two sweeps of a small 2D lattice cost more than its draws (L = 64 x 4096
+  // replicas: 11.7 against 9.0 us per sweep); in 3D the draws are dearer (L = 20 x 1024: 26 against 31)
+  if (d == 2 && block_resident(d, P) && sweeps < 3) return 0;
   if (bytes) *bytes = (size_t)sweeps * per_sweep;
   return sweeps;
 }
@@ -853,9 +842,8 @@ int64_t lds_chunk(ka_sim *s)
   if (!s->lds_acc_tried) {
     s->lds_acc_tried = true;
     size_t bytes = 0;
-    const int64_t sweeps = s->lattice && s->geom.d == 2 ? square_acc_plan(s->geom.P, s->W, &bytes)
-                           : s->lattice                 ? lds_acc_plan(s->geom.d, s->geom.L, s->R, &bytes)
-                                                        : lds_acc_plan_graph((int64_t)s->edges_total,
+    const int64_t sweeps = s->lattice ? block_acc_plan(s->geom.d, s->geom.P, s->W, &bytes)
+                                      : lds_acc_plan_graph((int64_t)s->edges_total,
                                                            max_class_edges(s->plan->class_start), s->z, s->R, &bytes);
     if (sweeps > 0 && dalloc(&s->lds_acc, bytes) == hipSuccess) {
       s->lds_acc_sweeps = sweeps;
@@ -966,8 +954,7 @@ hipError_t launch_lds(ka_sim *s, int64_t t_from, int64_t t_to, int q0, int q1, b
   if (s->lds_acc && a.n_sweeps > 0) {
     if (a.n_sweeps > s->lds_acc_sweeps) return hipErrorInvalidValue;
     a.acc = s->lds_acc;
-    a.acc_slots = s->lattice ? ka::lds_lattice_slots(s->geom.d, s->geom.P)
-                             : ka::lds_graph_slots(max_class_edges(s->plan->class_start));
+    if (!s->lattice) a.acc_slots = ka::lds_graph_slots(max_class_edges(s->plan->class_start));
     hipError_t e = ka::launch_lds_accept(a, s->lattice != 0, s->wpt, s->stream);
     if (e != hipSuccess) return e;
   }
@@ -1001,18 +988,20 @@ ka::SquareArgs square_args(const ka_sim *s, int64_t t0, int64_t sweeps)
   return a;
 }
 
-// Resident 2D launch covering sweeps [t_from, t_to) (at most lds_chunk of them) that also takes
-// observations obs[q0..q1) as snapshots (at most lds_snap_rows) and counts them.
+// Resident launch covering sweeps [t_from, t_to) (at most lds_chunk of them) that also takes
+// observations obs[q0..q1) as snapshots (at most lds_snap_rows), which are counted afterwards.
 hipError_t launch_resident(ka_sim *s, int64_t t_from, int64_t t_to, int q0, int q1)
 {
   if (t_to == t_from) return observe_rows(s, s->n, s->f, 0, q0, q1 - q0);
   ka::SquareArgs a = square_args(s, t_from, t_to - t_from);
-  hipError_t e = ka::launch_square_accept(a, s->stream);
   a.obs_times = s->obs_d + q0;
   a.n_obs = q1 - q0;
   a.snap = s->lds_snap;
   if (q1 > q0 && (!s->lds_snap || (size_t)(q1 - q0) > s->lds_snap_rows)) return hipErrorInvalidValue;
-  if (e == hipSuccess) e = ka::launch_square_resident(a, s->m, s->stream);
+  const bool flat = s->geom.d == 2;
+  hipError_t e = hipSuccess;
+  if (a.acc) e = flat ? ka::launch_square_accept(a, s->stream) : ka::launch_cube_accept(a, s->stream);
+  if (e == hipSuccess) e = flat ? ka::launch_square_resident(a, s->m, s->stream) : ka::launch_cube_resident(a, s->m, s->stream);
   if (e == hipSuccess && q1 > q0) {
     const size_t row_words = (size_t)s->N * (size_t)s->W;
     e = observe_rows(s, s->lds_snap, s->lds_snap + row_words, 2u * row_words, q0, q1 - q0);
@@ -1052,10 +1041,6 @@ hipError_t sweep_tiles(ka_sim *s, int64_t n)
 Route sweep_route(ka_sim *s)
 {
   const Route by = route(s);
-  if (by == Route::resident) {
-    (void)lds_chunk(s);
-    if (!s->lds_acc) return Route::passes;
-  }
   if (by == Route::tiles && !s->n_next && dalloc(&s->n_next, (size_t)s->N * (size_t)s->W * 8u) != hipSuccess) {
     (void)hipGetLastError();
     s->n_next = nullptr;
@@ -1175,7 +1160,11 @@ int ka_sim_batch_bytes(const ka_graph *g, int n_replicas, size_t *device_bytes)
     // observation snapshots
     size_t acc = 0;
     if (g->lattice) {
-      (void)lds_acc_plan(g->d, g->L, n_replicas, &acc);
+      // room for one class's words on each of 1024 threads' edge slots, for up to 8 MiB of sweeps
+      const int64_t P = g->N / (g->d == 2 ? 16 : 64);
+      const size_t slots = (size_t)(((g->d == 2 ? 4 : 16) * P + 1023) / 1024);
+      const size_t per_sweep = (size_t)(n_replicas / 64) * (size_t)(4 * g->d) * slots * 1024u * 8u;
+      if (per_sweep <= kLdsAccBudget && !(g->d == 3 && wpt == 2 && slots > 1)) acc = std::min<size_t>(kLdsChunk, kLdsAccBudget / per_sweep) * per_sweep;
     } else {
       std::vector<int> cs((size_t)g->C + 1, 0);
       for (int32_t c : g->ecls) cs[(size_t)c + 1] += 1;
@@ -1192,19 +1181,19 @@ extern "C" int ka_footprint(const ka_graph *g, int n_replicas, size_t *device_by
 {
   return ka_guard([&]() -> int {
     const int rc = ka_sim_batch_bytes(g, n_replicas, device_bytes);
-    if (rc != KA_OK || !g->lattice || g->d != 2) return rc;
+    if (rc != KA_OK || !g->lattice) return rc;
+    // what the sim's own sweeps on register blocks take beyond that: words drawn ahead, and
+    // snapshots or a second copy of n
+    const int64_t P = g->N / (g->d == 2 ? 16 : 64);
+    const bool small = block_resident(g->d, P);
+    if (g->d == 3 && !small) return KA_OK;
     const int wpt = ((n_replicas / 64) % 2 == 0) ? 2 : 1;
     const bool fits = ka::sweep_lds_bytes((int)g->N, wpt) + 4096 <= (size_t)ka::max_lds_bytes();
-    const int64_t P = g->N / 16;
-    if (!fits) {
-      // words drawn ahead (those of a sim whose word plane fits in LDS are counted above) and, for
-      // a lattice in one workgroup, snapshots
-      size_t acc = 0;
-      (void)square_acc_plan((int)P, n_replicas / 64, &acc);
-      const size_t row = lds_snap_row_bytes(g->N, n_replicas);
-      *device_bytes += acc + (P <= ka::kSquareResidentP ? (kLdsSnapBudget / row) * row : 0);
-    }
-    if (P > ka::kSquareResidentP) *device_bytes += (size_t)g->N * (size_t)(n_replicas / 64) * 8u;   // second copy of n
+    const size_t row = lds_snap_row_bytes(g->N, n_replicas);
+    size_t draws = 0;
+    (void)block_acc_plan(g->d, P, n_replicas / 64, &draws);   // those of a sim whose word plane fits in LDS are counted there
+    if (!fits) *device_bytes += draws + (small ? (kLdsSnapBudget / row) * row : 0);
+    if (!small) *device_bytes += (size_t)g->N * (size_t)(n_replicas / 64) * 8u;
     return KA_OK;
   });
 }

@@ -76,7 +76,8 @@ struct PassGraph {
   uint32_t c_end;
 };
 
-// Whole sweep loop inside one workgroup per plane (plane in LDS).
+// Whole sweep loop of a general graph or a tiny 3D lattice inside one workgroup per plane (plane in
+// LDS).
 struct SweepLds {
   u64 *n;
   u64 *f;
@@ -100,7 +101,7 @@ struct SweepLds {
   int R;
   uint32_t key0, key1;
   // acceptance words of these sweeps generated beforehand (null: drawn in the loop).
-  // Lattices: element (((plane * n_sweeps + s) * C + c) * acc_slots + j) * 1024 + thread.
+  // Lattices: element ((plane * n_sweeps + s) * C + c) * 16 P + edge of the class.
   // Graphs: element (plane * n_sweeps + s) * E + k for class-sorted edge k (E = stride), and
   // acc_slots is the most edges any class gives one of the 1024 threads.
   u64 *acc;
@@ -111,7 +112,7 @@ struct SweepLds {
   u64 *snap;
 };
 
-// 2D lattices, one word at a time (ka_square.hip).
+// Lattices on register blocks, one word at a time (ka_square.hip, ka_cube.hip).
 struct SquareArgs {
   u64 *n;
   u64 *f;
@@ -120,7 +121,7 @@ struct SquareArgs {
   int W, wpt;                // words of the sim, words per element of its layout
   int noise;                 // 0: acceptance bit per replica, 1: shared by all replicas
   uint32_t t0, key0, key1;
-  u64 *acc;                  // acceptance words drawn ahead (tiles: null = drawn in the sweep)
+  u64 *acc;                  // acceptance words drawn ahead (null: drawn in the sweep)
   int n_sweeps;              // sweeps that acc holds, from t0 (resident: all of them run)
   int sweep;                 // tiles: the first of them that this launch runs
   const int64_t *obs_times;  // resident: observations as snapshots (layout of SweepLds::snap)
@@ -129,6 +130,10 @@ struct SquareArgs {
 };
 // Positions (4 x 4 blocks) of a lattice that one workgroup holds.
 constexpr int kSquareResidentP = 512;
+// The same for 3D lattices in one workgroup per word (fewer positions than kCubeMinP: ka_lds.hip).
+constexpr int kCubeResidentP = 128, kCubeMinP = 64;
+hipError_t launch_cube_accept(const SquareArgs &a, hipStream_t s);
+hipError_t launch_cube_resident(const SquareArgs &a, int m, hipStream_t s);
 hipError_t launch_square_accept(const SquareArgs &a, hipStream_t s);
 hipError_t launch_square_resident(const SquareArgs &a, int m, hipStream_t s);
 int square_sweeps_per_launch(const SquareArgs &a);
@@ -176,8 +181,7 @@ hipError_t launch_pass_graph(const PassGraph &a, int z, int m, int wpt, hipStrea
 // launch of one workgroup per plane.
 constexpr int kTailEdges = 512;
 hipError_t launch_tail_graph(const PassGraph &a, int z, int m, int wpt, hipStream_t s);
-hipError_t launch_sweep_lds(const SweepLds &a, bool lattice, int zdeg, int m, int wpt,
-                            size_t lds_bytes, hipStream_t s);
+hipError_t launch_sweep_lds(const SweepLds &a, bool lattice, int zdeg, int m, int wpt, size_t lds_bytes, hipStream_t s);
 hipError_t launch_init(const InitArgs &a, int R, int wpt, hipStream_t s);
 hipError_t launch_observe(const ObserveArgs &a, int wpt, hipStream_t s);
 // Fixed device scratch of the observation entry point that allocates nothing: 3 counts per
@@ -190,16 +194,12 @@ hipError_t observe_scratch_setup(int device);
 unsigned long long *observe_scratch(int device);
 hipError_t launch_fill_u64(unsigned long long *p, int n, unsigned long long v, hipStream_t s);
 size_t sweep_lds_bytes(int N, int wpt);
-// Edge slots per thread of the LDS lattice sweep (edges per class over its 1024 threads).
-int lds_lattice_slots(int d, int P);
-// Whether the LDS lattice sweep takes pre-generated acceptance words for this layout.
-bool lds_accept_supported(int d, int wpt, int slots);
 // Edge slots per thread of the LDS graph sweep for its largest class, and the most it takes
 // pre-generated acceptance words for.
 int lds_graph_slots(int max_class_edges);
 constexpr int kLdsGraphAcceptSlots = 3;
 bool lds_graph_accept_supported(int z, int wpt);
-// Acceptance words of a.n_sweeps sweeps for the LDS lattice or graph sweep, into a.acc.
+// Acceptance words of a.n_sweeps sweeps for the LDS sweep, into a.acc.
 hipError_t launch_lds_accept(const SweepLds &a, bool lattice, int wpt, hipStream_t s);
 
 // Spatial four-point sums (ka_pairs.hip).

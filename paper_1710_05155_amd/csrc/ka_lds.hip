@@ -1,4 +1,5 @@
-// ka_lds.hip -- LDS-resident sweep loop for instances whose word plane fits in LDS (gfx950).
+// ka_lds.hip -- LDS-resident sweep loop for general graphs whose word plane fits in LDS, and for 3D
+// lattices of fewer than kCubeMinP positions (gfx950).
 //
 // Method: Boccagna, arXiv 1710.05155; the per-edge bit logic lives in ka_device.h.
 #include "ka_device.h"
@@ -9,9 +10,6 @@ namespace {
 using namespace dev;
 
 constexpr int kLdsBlock = 1024;
-// Edges per thread and class on a lattice in LDS: a plane that fits (N * wpt <= 9984 words
-// per array) has at most 2496 edges per class.
-constexpr int kLdsSlots = 3;
 
 template <int WPT>
 __device__ void lds_observe(const SweepLds &a, const u64 *sn, const u64 *sf, int plane,
@@ -108,55 +106,88 @@ __device__ void lds_observe_due(const SweepLds &a, const u64 *sn, const u64 *sf,
   }
 }
 
-// Element of the pre-generated acceptance words of sweep s (relative to t0), class c, slot j
-// for this thread.
-__device__ __forceinline__ int acc_element(const SweepLds &a, int plane, int s, int c, int j)
+// Edge k of class c of a 3D lattice: the k / P-th lower-endpoint sublattice at position k % P.
+__device__ __forceinline__ Site class_edge(const LatticeGeom &g, int c, int k)
 {
-  return (((plane * a.n_sweeps + s) * a.C + c) * a.acc_slots + j) * kLdsBlock + (int)threadIdx.x;
+  const int q = k / g.P;
+  return decode(g, 3, class_sublattice(3, c >> 2, c & 3, q), k - q * g.P);
 }
 
 // Acceptance words of sweeps t0 .. t0 + n_sweeps - 1 for k_sweep_lds_lattice: one workgroup per
-// (sweep, class) and plane, each thread drawing the words of its edge slots exactly as the sweep
-// loop maps them (the same sublattice, position and canonical edge id).  The words do not
-// depend on the state, so the whole device draws them ahead of the single-workgroup loop.
-template <int D, int WPT>
+// (sweep, class) and plane, a thread per edge.  The words do not depend on the state, so the whole
+// device draws them ahead of the single-workgroup loop.
+template <int WPT>
 __global__ __launch_bounds__(kLdsBlock) void k_lds_accept_lattice(SweepLds a)
 {
-  const int sc = (int)blockIdx.x;
-  const int s = sc / a.C, c = sc - s * a.C;
+  const int s = (int)blockIdx.x / a.C, c = (int)blockIdx.x - s * a.C;
   const int plane = (int)blockIdx.y;
-  const int mu = c >> 2;
-  constexpr int nsub = D == 2 ? 4 : 16;
-  const int per_class = nsub * a.g.P;
-  for (int j = 0; j < a.acc_slots; ++j) {
-    const int k = (int)threadIdx.x + j * kLdsBlock;
-    if (k >= per_class) break;
-    const int q = k / a.g.P;
-    const int sub = class_sublattice(D, mu, c & 3, q);
-    const Site si = decode(a.g, D, sub, k - q * a.g.P);
-    const uint32_t e = (uint32_t)canonical(a.g, D, si) * (uint32_t)D + (uint32_t)mu;
-    u64 r[WPT];
-    accept_words<WPT>(a.t0 + (uint32_t)s, (uint32_t)c, e, plane, a.key0, a.key1, a.noise, r);
-    Elem<WPT> v;
+  const int k = (int)threadIdx.x;
+  if (k >= 16 * a.g.P) return;
+  const uint32_t e = (uint32_t)canonical(a.g, 3, class_edge(a.g, c, k)) * 3u + (uint32_t)(c >> 2);
+  u64 r[WPT];
+  accept_words<WPT>(a.t0 + (uint32_t)s, (uint32_t)c, e, plane, a.key0, a.key1, a.noise, r);
+  Elem<WPT> v;
 #pragma unroll
-    for (int w = 0; w < WPT; ++w) v.w[w] = r[w];
-    st<WPT>(a.acc, acc_element(a, plane, s, c, j), v);
-  }
+  for (int w = 0; w < WPT; ++w) v.w[w] = r[w];
+  st<WPT>(a.acc, ((plane * a.n_sweeps + s) * a.C + c) * 16 * a.g.P + k, v);
 }
 
-// One lattice edge of the LDS sweep with its acceptance words given.
-template <int D, int MU, int WPT>
-__device__ __forceinline__ void lattice_edge_given(u64 *nb, u64 *fb, const LatticeGeom &g,
-                                                   const Site &si, const Elem<WPT> &rw, int m)
+// A thread per edge of a class (at most 16 kCubeMinP of them), n and f in LDS.  With words drawn
+// ahead (GIVEN) those of the next class are loaded while this class is processed.
+template <int WPT, bool GIVEN>
+__global__ __launch_bounds__(kLdsBlock) void k_sweep_lds_lattice(SweepLds a, int m)
 {
-  constexpr int K = 2 * D - 1;
-  int i, j, ii[K], jj[K];
-  uint32_t e;
-  lattice_edge_indices<D, MU>(g, si, i, j, ii, jj, e);
-  edge_update_with<K, WPT>(nb, fb, i, j, ii, jj, m, [&](u64 (&r)[WPT]) {
+  extern __shared__ u64 lds[];
+  __shared__ unsigned cnt[3 * 64 * WPT];
+  u64 *sn = lds;
+  u64 *sf = lds + (size_t)a.N * WPT;
+  const int plane = blockIdx.x;
+  lds_load<WPT>(a, sn, sf, plane);
+  int qo = 0;
+  lds_observe_due<WPT>(a, sn, sf, plane, qo, (int64_t)a.t0, cnt);
+  const int k = (int)threadIdx.x;
+  const int per_class = 16 * a.g.P;
+  // the division and the block coordinates are done once; per class only the residues change
+  const int q = k / a.g.P;
+  const Site site = decode(a.g, 3, 0, k - q * a.g.P);
+  Elem<WPT> next;
+  if (GIVEN && k < per_class) next = ld<WPT>(a.acc, plane * a.n_sweeps * a.C * per_class + k);
+  for (int s = 0; s < a.n_sweeps; ++s) {
+    const uint32_t t = a.t0 + (uint32_t)s;
+    for (int c = 0; c < a.C; ++c) {
+      const int mu = c >> 2;
+      const int sub = class_sublattice(3, mu, c & 3, q);
+      Site si = site;
+      si.a[0] = sub & 3;
+      si.a[1] = (sub >> 2) & 3;
+      si.a[2] = (sub >> 4) & 3;
+      si.idx += sub * a.g.P;
+      const Elem<WPT> rw = next;
+      const int step = (plane * a.n_sweeps + s) * a.C + c + 1;
+      if (GIVEN && k < per_class && (c + 1 < a.C || s + 1 < a.n_sweeps)) next = ld<WPT>(a.acc, step * per_class + k);
+      const auto edge = [&](auto MU) {
+        int i, j, ii[5], jj[5];
+        uint32_t e;
+        lattice_edge_indices<3, decltype(MU)::value>(a.g, si, i, j, ii, jj, e);
+        edge_update_with<5, WPT>(sn, sf, i, j, ii, jj, m, [&](u64 (&r)[WPT]) {
+          if constexpr (GIVEN) {
 #pragma unroll
-    for (int w = 0; w < WPT; ++w) r[w] = rw.w[w];
-  });
+            for (int w = 0; w < WPT; ++w) r[w] = rw.w[w];
+          } else {
+            accept_words<WPT>(t, (uint32_t)c, e, plane, a.key0, a.key1, a.noise, r);
+          }
+        });
+      };
+      if (k < per_class) {
+        if (mu == 0) edge(std::integral_constant<int, 0>());
+        else if (mu == 1) edge(std::integral_constant<int, 1>());
+        else edge(std::integral_constant<int, 2>());
+      }
+      __syncthreads();
+    }
+    lds_observe_due<WPT>(a, sn, sf, plane, qo, (int64_t)t + 1, cnt);
+  }
+  lds_store<WPT>(a, sn, sf, plane);
 }
 
 // Acceptance words of sweeps t0 .. t0 + n_sweeps - 1 for k_sweep_lds_graph: blockIdx.x runs
@@ -178,92 +209,6 @@ __global__ __launch_bounds__(kLdsBlock) void k_lds_accept_graph(SweepLds a)
 #pragma unroll
   for (int w = 0; w < WPT; ++w) rw.w[w] = r[w];
   st<WPT>(a.acc, (plane * a.n_sweeps + s) * E + k, rw);
-}
-
-// SLOTS: edge slots per thread the kernel is compiled for (the class size over 1024, rounded
-// up, must not exceed it).
-template <int D, int WPT, bool GIVEN, int SLOTS = kLdsSlots>
-__global__ __launch_bounds__(kLdsBlock) void k_sweep_lds_lattice(SweepLds a, int m)
-{
-  extern __shared__ u64 lds[];
-  __shared__ unsigned cnt[3 * 64 * WPT];
-  u64 *sn = lds;
-  u64 *sf = lds + (size_t)a.N * WPT;
-  const int plane = blockIdx.x;
-  lds_load<WPT>(a, sn, sf, plane);
-  int qo = 0;
-  lds_observe_due<WPT>(a, sn, sf, plane, qo, (int64_t)a.t0, cnt);
-  constexpr int nsub = D == 2 ? 4 : 16;   // lower-endpoint sublattices per class
-  const int per_class = nsub * a.g.P;
-  // This thread's edges are the same in every class: slot j is edge k = tid + j * blockDim of
-  // the class, the q-th lower-endpoint sublattice at position pos.  The divisions and the
-  // block coordinates of pos are done once, here; per class only the residues change.
-  const int tid = (int)threadIdx.x;
-  int slot_q[SLOTS];
-  Site slot_site[SLOTS];
-#pragma unroll
-  for (int j = 0; j < SLOTS; ++j) {
-    const int k = tid + j * kLdsBlock;
-    const int q = k / a.g.P;
-    slot_q[j] = q;
-    slot_site[j] = decode(a.g, D, 0, k - q * a.g.P);   // idx = pos, residues 0
-  }
-  // With pre-generated acceptance words, those of the next class are loaded while this
-  // class is processed (the loads stay in flight across the barrier).
-  Elem<WPT> rnext[SLOTS];
-  if constexpr (GIVEN) {
-#pragma unroll
-    for (int j = 0; j < SLOTS; ++j)
-      if (tid + j * kLdsBlock < per_class) rnext[j] = ld<WPT>(a.acc, acc_element(a, plane, 0, 0, j));
-  }
-  for (int s = 0; s < a.n_sweeps; ++s) {
-    const uint32_t t = a.t0 + (uint32_t)s;
-    for (int c = 0; c < a.C; ++c) {
-      const int mu = c >> 2;
-      Elem<WPT> rcur[SLOTS];
-      if constexpr (GIVEN) {
-        const int s2 = c + 1 < a.C ? s : s + 1;
-        const int c2 = c + 1 < a.C ? c + 1 : 0;
-#pragma unroll
-        for (int j = 0; j < SLOTS; ++j) {
-          rcur[j] = rnext[j];
-          if (s2 < a.n_sweeps && tid + j * kLdsBlock < per_class)
-            rnext[j] = ld<WPT>(a.acc, acc_element(a, plane, s2, c2, j));
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < SLOTS; ++j) {
-        if (tid + j * kLdsBlock >= per_class) break;
-        const int sub = class_sublattice(D, mu, c & 3, slot_q[j]);
-        Site si = slot_site[j];
-        si.a[0] = sub & 3;
-        si.a[1] = (sub >> 2) & 3;
-        si.a[2] = (sub >> 4) & 3;
-        si.idx += sub * a.g.P;
-        if constexpr (GIVEN) {
-          if (mu == 0)
-            lattice_edge_given<D, 0, WPT>(sn, sf, a.g, si, rcur[j], m);
-          else if (mu == 1)
-            lattice_edge_given<D, 1, WPT>(sn, sf, a.g, si, rcur[j], m);
-          else if constexpr (D == 3)
-            lattice_edge_given<D, 2, WPT>(sn, sf, a.g, si, rcur[j], m);
-          continue;
-        }
-        if (mu == 0)
-          lattice_edge_at<D, 0, WPT>(sn, sf, a.g, si, plane, m, t, (uint32_t)c, a.key0, a.key1,
-                                     a.noise);
-        else if (mu == 1)
-          lattice_edge_at<D, 1, WPT>(sn, sf, a.g, si, plane, m, t, (uint32_t)c, a.key0, a.key1,
-                                     a.noise);
-        else if constexpr (D == 3)
-          lattice_edge_at<D, 2, WPT>(sn, sf, a.g, si, plane, m, t, (uint32_t)c, a.key0, a.key1,
-                                     a.noise);
-      }
-      __syncthreads();
-    }
-    lds_observe_due<WPT>(a, sn, sf, plane, qo, (int64_t)t + 1, cnt);
-  }
-  lds_store<WPT>(a, sn, sf, plane);
 }
 
 // GIVEN: the acceptance words come from a.acc (every class has at most kLdsGraphAcceptSlots
@@ -353,14 +298,6 @@ hipError_t set_lds(Kern k, size_t bytes)
 
 size_t sweep_lds_bytes(int N, int wpt) { return (size_t)2 * (size_t)N * (size_t)wpt * 8u; }
 
-int lds_lattice_slots(int d, int P) { return ((d == 2 ? 4 : 16) * P + kLdsBlock - 1) / kLdsBlock; }
-
-// The sweep loop with given acceptance words keeps the next class's words in registers.  For
-// 3D word pairs it is compiled for one edge slot per thread, the most a 3D plane of word pairs
-// that fits in LDS needs (L = 16: 1024 edges per class); three slots would not fit the 128
-// registers a 1024-thread workgroup allows.
-bool lds_accept_supported(int d, int wpt, int slots) { return !(d == 3 && wpt == 2 && slots > 1); }
-
 int lds_graph_slots(int max_class_edges) { return (max_class_edges + kLdsBlock - 1) / kLdsBlock; }
 
 // With given words the graph sweep holds each slot's record, neighbour ids and words in
@@ -371,24 +308,21 @@ bool lds_graph_accept_supported(int z, int wpt) { return !(z == 6 && wpt == 2); 
 hipError_t launch_lds_accept(const SweepLds &a, bool lattice, int wpt, hipStream_t s)
 {
   const int planes = (a.R / 64) / wpt;
-  if (!lattice) {
-    const int E = (int)a.stride;
-    const int nblk = (E + kLdsBlock - 1) / kLdsBlock;
-    if (!a.acc || a.n_sweeps < 1 || E < 1 || a.acc_slots < 1 || a.acc_slots > kLdsGraphAcceptSlots ||
-        (long long)a.n_sweeps * nblk > 0x7FFFFFFFLL)
-      return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(a.n_sweeps * nblk), (unsigned)planes);
-    if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_graph<2>), grid, dim3(kLdsBlock), 0, s, a);
-    else hipLaunchKernelGGL((k_lds_accept_graph<1>), grid, dim3(kLdsBlock), 0, s, a);
+  if (lattice) {
+    if (!a.acc || a.n_sweeps < 1 || a.g.d != 3 || a.g.P >= kCubeMinP) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(a.n_sweeps * a.C), (unsigned)planes), block((unsigned)((16 * a.g.P + 63) / 64 * 64));
+    if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_lattice<2>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_lds_accept_lattice<1>), grid, block, 0, s, a);
     return hipGetLastError();
   }
-  if (!a.acc || a.n_sweeps < 1 || a.acc_slots < 1 || a.acc_slots > kLdsSlots ||
-      a.acc_slots != lds_lattice_slots(a.g.d, a.g.P) || !lds_accept_supported(a.g.d, wpt, a.acc_slots))
+  const int E = (int)a.stride;
+  const int nblk = (E + kLdsBlock - 1) / kLdsBlock;
+  if (!a.acc || a.n_sweeps < 1 || E < 1 || a.acc_slots < 1 || a.acc_slots > kLdsGraphAcceptSlots ||
+      (long long)a.n_sweeps * nblk > 0x7FFFFFFFLL)
     return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(a.n_sweeps * a.C), (unsigned)planes);
-  const dim3 block(kLdsBlock);
-  if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_lattice<3, 2>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((k_lds_accept_lattice<3, 1>), grid, block, 0, s, a);
+  const dim3 grid((unsigned)(a.n_sweeps * nblk), (unsigned)planes);
+  if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_graph<2>), grid, dim3(kLdsBlock), 0, s, a);
+  else hipLaunchKernelGGL((k_lds_accept_graph<1>), grid, dim3(kLdsBlock), 0, s, a);
   return hipGetLastError();
 }
 
@@ -400,19 +334,29 @@ int max_lds_bytes()
   return v;
 }
 
-hipError_t launch_sweep_lds(const SweepLds &a, bool lattice, int zdeg, int m, int wpt,
-                            size_t lds_bytes, hipStream_t s)
+hipError_t launch_sweep_lds(const SweepLds &a, bool lattice, int zdeg, int m, int wpt, size_t lds_bytes, hipStream_t s)
 {
   const int planes = (a.R / 64) / wpt;
   const dim3 grid((unsigned)planes);
-  const dim3 block(kLdsBlock);
+  dim3 block(kLdsBlock);
   hipError_t e = hipSuccess;
-#define KA_LDS_L(D, W, G)                                                         \
+  if (lattice) {
+    if (a.g.d != 3 || a.g.P >= kCubeMinP) return hipErrorInvalidValue;
+    block.x = (unsigned)((16 * a.g.P + 63) / 64 * 64);   // fewer waves, cheaper barriers
+#define KA_LDS_L(W, G)                                                            \
   do {                                                                            \
-    e = set_lds(k_sweep_lds_lattice<D, W, G>, lds_bytes);                         \
+    e = set_lds(k_sweep_lds_lattice<W, G>, lds_bytes);                            \
     if (e == hipSuccess)                                                          \
-      hipLaunchKernelGGL((k_sweep_lds_lattice<D, W, G>), grid, block, lds_bytes, s, a, m); \
+      hipLaunchKernelGGL((k_sweep_lds_lattice<W, G>), grid, block, lds_bytes, s, a, m); \
   } while (0)
+    if (wpt == 2) {
+      if (a.acc) KA_LDS_L(2, true); else KA_LDS_L(2, false);
+    } else {
+      if (a.acc) KA_LDS_L(1, true); else KA_LDS_L(1, false);
+    }
+#undef KA_LDS_L
+    return e == hipSuccess ? hipGetLastError() : e;
+  }
 #define KA_LDS_G1(Z, W, G)                                                        \
   do {                                                                            \
     e = set_lds(k_sweep_lds_graph<Z, W, G>, lds_bytes);                           \
@@ -423,36 +367,19 @@ hipError_t launch_sweep_lds(const SweepLds &a, bool lattice, int zdeg, int m, in
   do {                                                                            \
     if (a.acc) KA_LDS_G1(Z, W, true); else KA_LDS_G1(Z, W, false);                 \
   } while (0)
-  if (lattice && (a.g.d != 3 || 16 * a.g.P > kLdsSlots * kLdsBlock)) return hipErrorInvalidValue;
-  if (lattice) {
-    if (a.acc && !lds_accept_supported(a.g.d, wpt, lds_lattice_slots(a.g.d, a.g.P))) return hipErrorInvalidValue;
-    const bool g = a.acc != nullptr;
-    if (wpt == 2) {
-      if (g) {
-        e = set_lds(k_sweep_lds_lattice<3, 2, true, 1>, lds_bytes);
-        if (e == hipSuccess)
-          hipLaunchKernelGGL((k_sweep_lds_lattice<3, 2, true, 1>), grid, block, lds_bytes, s, a, m);
-      } else {
-        KA_LDS_L(3, 2, false);
-      }
-    } else if (g) KA_LDS_L(3, 1, true);
-    else KA_LDS_L(3, 1, false);
-  } else {
-    if (a.acc && (a.acc_slots < 1 || a.acc_slots > kLdsGraphAcceptSlots || !lds_graph_accept_supported(zdeg, wpt)))
-      return hipErrorInvalidValue;
-    switch (zdeg * 4 + wpt) {
-      case 3 * 4 + 1: KA_LDS_G(3, 1); break;
-      case 3 * 4 + 2: KA_LDS_G(3, 2); break;
-      case 4 * 4 + 1: KA_LDS_G(4, 1); break;
-      case 4 * 4 + 2: KA_LDS_G(4, 2); break;
-      case 5 * 4 + 1: KA_LDS_G(5, 1); break;
-      case 5 * 4 + 2: KA_LDS_G(5, 2); break;
-      case 6 * 4 + 1: KA_LDS_G(6, 1); break;
-      case 6 * 4 + 2: KA_LDS_G1(6, 2, false); break;   // see lds_graph_accept_supported
-      default: return hipErrorInvalidValue;
-    }
+  if (a.acc && (a.acc_slots < 1 || a.acc_slots > kLdsGraphAcceptSlots || !lds_graph_accept_supported(zdeg, wpt)))
+    return hipErrorInvalidValue;
+  switch (zdeg * 4 + wpt) {
+    case 3 * 4 + 1: KA_LDS_G(3, 1); break;
+    case 3 * 4 + 2: KA_LDS_G(3, 2); break;
+    case 4 * 4 + 1: KA_LDS_G(4, 1); break;
+    case 4 * 4 + 2: KA_LDS_G(4, 2); break;
+    case 5 * 4 + 1: KA_LDS_G(5, 1); break;
+    case 5 * 4 + 2: KA_LDS_G(5, 2); break;
+    case 6 * 4 + 1: KA_LDS_G(6, 1); break;
+    case 6 * 4 + 2: KA_LDS_G1(6, 2, false); break;   // see lds_graph_accept_supported
+    default: return hipErrorInvalidValue;
   }
-#undef KA_LDS_L
 #undef KA_LDS_G
 #undef KA_LDS_G1
   if (e != hipSuccess) return e;

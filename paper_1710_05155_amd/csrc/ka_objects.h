@@ -94,7 +94,7 @@ struct ka_sim {
                                   // of at most kTailEdges edges (C if that run is shorter than 2)
   size_t lds_bytes = 0;
   bool lds_fits = false;
-  ka::u64 *lds_acc = nullptr;     // LDS lattice sweep: pre-generated acceptance words
+  ka::u64 *lds_acc = nullptr;     // acceptance words drawn ahead (LDS graph sweep, register blocks)
   int64_t lds_acc_sweeps = 0;     // sweeps lds_acc holds (0: words drawn in the loop)
   bool lds_acc_tried = false;
   ka::u64 *lds_snap = nullptr;    // LDS sweep: snapshots of n and f taken at observation times

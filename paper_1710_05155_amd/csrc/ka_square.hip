@@ -192,8 +192,8 @@ __device__ __forceinline__ T *sublattice_word(T *base, const SquareArgs &a, int 
   return base + ((size_t)(word / a.wpt) * (size_t)a.g.N + (size_t)sub * (size_t)a.g.P) * (size_t)a.wpt + (size_t)(word % a.wpt);
 }
 
-// Acceptance words of sweeps t0 .. t0 + n_sweeps - 1, a.acc[((word * n_sweeps + s) * 32 + c * 4 + q) * P + pos]:
-// a thread draws its position's four edges of a class, and one Philox call serves two words.
+// Acceptance words of sweeps t0 .. t0 + n_sweeps - 1: a.acc[((word * n_sweeps + s) * 32 + c * 4 + q) * P + pos].  A thread draws its position's
+// four edges of a class, and one Philox call serves two words.
 __global__ __launch_bounds__(256) void k_square_accept(SquareArgs a)
 {
   const int pos = (int)blockIdx.x * (int)blockDim.x + (int)threadIdx.x;
@@ -211,12 +211,13 @@ __global__ __launch_bounds__(256) void k_square_accept(SquareArgs a)
                     r[q]);
   }
 #pragma unroll
-  for (int w = 0; w < 2; ++w)
-    if (2 * pair + w < a.W) {
-      u64 *acc = a.acc + (((size_t)(2 * pair + w) * a.n_sweeps + s) * 32u + (size_t)c * 4u) * (size_t)a.g.P;
+  for (int w = 0; w < 2; ++w) {
+    const int word = 2 * pair + w;
+    if (word >= a.W) continue;
+    u64 *acc = a.acc + (((size_t)word * a.n_sweeps + s) * 32u + (size_t)c * 4u) * (size_t)a.g.P;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) (acc + (size_t)q * (size_t)a.g.P)[pos] = r[q][w];
-    }
+    for (int q = 0; q < 4; ++q) (acc + (size_t)q * (size_t)a.g.P)[pos] = r[q][w];
+  }
 }
 
 // The thread's block from n at position `from` of the sublattice layout, into registers and LDS
@@ -235,7 +236,7 @@ __device__ __forceinline__ void load_block(Square<P> &t, const SquareArgs &a, in
 }
 
 // Bound by issue and latency on one CU per word (0.44 us per class at 256 blocks).
-template <int NT>
+template <int NT, bool GIVEN>
 __global__ __launch_bounds__(NT) void k_square_resident(SquareArgs a, int m)
 {
   extern __shared__ u64 sq_lds[];
@@ -263,20 +264,33 @@ __global__ __launch_bounds__(NT) void k_square_resident(SquareArgs a, int m)
   __syncthreads();
   SquareDraw g{};
   g.P = a.g.P;
-  g.acc = a.acc + (size_t)word * a.n_sweeps * 32u * (size_t)a.g.P;
-  g.pos = (unsigned)p;
-  constexpr int D = 4;   // classes of words in flight: they cover the words' latency
-  u64 r[D][4];
+  constexpr int D = GIVEN ? 4 : 0;   // classes of words in flight: they cover the words' latency
+  u64 r[D ? D : 1][4];
+  if constexpr (GIVEN) {
+    g.acc = a.acc + (size_t)word * a.n_sweeps * 32u * (size_t)a.g.P;
+    g.pos = (unsigned)p;
 #pragma unroll
-  for (int c = 0; c < D; ++c) g.load(c, r[c]);
+    for (int c = 0; c < D; ++c) g.load(c, r[c]);
+  } else {
+    g.t = a.t0;
+    g.key0 = a.key0;
+    g.key1 = a.key1;
+    g.site = (uint32_t)(4 * p0) + (uint32_t)(4 * p1) * (uint32_t)a.g.L;
+    g.L = (uint32_t)a.g.L;
+    g.word = word;
+    g.noise = a.noise;
+  }
   const auto store = [&](u64 *n, u64 *f) {
     if (!mine) return;
+    // not known to be the same from call to call, so that the addresses are not kept (spilled) over the sweeps
+    int to = word;
+    asm volatile("" : "+s"(to));
 #pragma unroll
     for (int y = 0; y < 4; ++y)
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        sublattice_word(n, a, word, x + 4 * y)[(unsigned)(pos * a.wpt)] = t.n[y][x];
-        sublattice_word(f, a, word, x + 4 * y)[(unsigned)(pos * a.wpt)] = t.f[y][x];
+        sublattice_word(n, a, to, x + 4 * y)[(unsigned)(pos * a.wpt)] = t.n[y][x];
+        sublattice_word(f, a, to, x + 4 * y)[(unsigned)(pos * a.wpt)] = t.f[y][x];
       }
   };
   // observations: n and f as they are, for the observation kernel to count after this launch
@@ -292,6 +306,7 @@ __global__ __launch_bounds__(NT) void k_square_resident(SquareArgs a, int m)
   for (int s = 0; s < a.n_sweeps; ++s) {
     t.template sweep<D>(r, g, m, s + 1 < a.n_sweeps);
     g.acc += 32u * (size_t)a.g.P;
+    g.t += 1;
     observe((int64_t)a.t0 + s + 1);
   }
   store(a.n, a.f);
@@ -401,15 +416,15 @@ hipError_t launch_tile(const SquareArgs &a, int m, hipStream_t s)
   return hipGetLastError();
 }
 
-template <int NT>
+template <int NT, bool GIVEN>
 hipError_t launch_resident(const SquareArgs &a, int m, hipStream_t s)
 {
   const int threads = (a.g.P + 63) / 64 * 64;
   const size_t lds = (size_t)16 * NT * sizeof(u64);
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_square_resident<NT>),
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_square_resident<NT, GIVEN>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_square_resident<NT>), dim3((unsigned)a.W), dim3((unsigned)threads), lds, s, a, m);
+  hipLaunchKernelGGL((k_square_resident<NT, GIVEN>), dim3((unsigned)a.W), dim3((unsigned)threads), lds, s, a, m);
   return hipGetLastError();
 }
 
@@ -426,8 +441,12 @@ hipError_t launch_square_accept(const SquareArgs &a, hipStream_t s)
 
 hipError_t launch_square_resident(const SquareArgs &a, int m, hipStream_t s)
 {
-  if (!a.acc || a.g.d != 2 || a.g.P > kSquareResidentP || a.n_sweeps < 1) return hipErrorInvalidValue;
-  return a.g.P <= 64 ? launch_resident<64>(a, m, s) : a.g.P <= 256 ? launch_resident<256>(a, m, s) : launch_resident<512>(a, m, s);
+  if (a.g.d != 2 || a.g.P > kSquareResidentP || a.n_sweeps < 1) return hipErrorInvalidValue;
+  if (a.acc)
+    return a.g.P <= 64 ? launch_resident<64, true>(a, m, s) : a.g.P <= 256 ? launch_resident<256, true>(a, m, s)
+                                                            : launch_resident<512, true>(a, m, s);
+  return a.g.P <= 64 ? launch_resident<64, false>(a, m, s) : a.g.P <= 256 ? launch_resident<256, false>(a, m, s)
+                                                           : launch_resident<512, false>(a, m, s);
 }
 
 // With one tile per CU a launch's fixed cost is shared by its sweeps, and the deeper halos cost
