@@ -1637,28 +1637,49 @@ extern "C" int ka_observe_pairs(ka_sim *s, int r2_max, int64_t *S2, int64_t *S11
     if (s->W > 16) return fail(KA_EINVAL, "spatial pair sums support up to 1024 replicas");
     if (!s->lattice) return pair_sums_graph(s, r2_max, S2, S11, count);
     const int d = s->geom.d, L = s->geom.L;
-    // every displacement of the torus once, components in the minimum image (|c| <= L/2)
+    // Every displacement of the torus within the radius, components in the minimum image
+    // (-L/2, L/2]; of a displacement and its opposite, whose sums are the same, the one with the
+    // larger (dz, dy, dx) is computed.
+    int halo = 0;
+    while (halo < L / 2 && (halo + 1) * (halo + 1) <= r2_max) ++halo;
+    int rows = 0, words = 0;
+    const bool tiles = ka::pairs_tile_rows(L, halo, r2_max, &rows, &words);
     std::vector<int4> disp;
     std::vector<int64_t> cnt((size_t)r2_max + 1, 0);
-    const int n_total = d == 2 ? L * L : L * L * L;
-    for (int q = 0; q < n_total; ++q) {
-      int c[3] = {q % L, (q / L) % L, d == 3 ? q / (L * L) : 0};
-      int r2 = 0;
-      for (int k = 0; k < d; ++k) {
-        if (c[k] > L / 2) c[k] -= L;
-        r2 += c[k] * c[k];
-      }
-      if (r2 > r2_max) continue;
-      disp.push_back(make_int4(c[0], c[1], c[2], r2));
-      cnt[(size_t)r2] += 1;
+    std::vector<int> start;
+    const int hz = d == 3 ? halo : 0;
+    const auto opposite = [L](int c) { return 2 * c == L ? c : -c; };
+    for (int dz = -hz; dz <= hz; ++dz) {
+      if (dz >= 0) start.push_back((int)disp.size());
+      for (int dy = -halo; dy <= halo; ++dy)
+        for (int dx = -halo; dx <= halo; ++dx) {
+          const int r2 = dx * dx + dy * dy + dz * dz;
+          if (r2 > r2_max || 2 * dx == -L || 2 * dy == -L || 2 * dz == -L) continue;
+          cnt[(size_t)r2] += 1;
+          const int oz = opposite(dz), oy = opposite(dy), ox = opposite(dx);
+          const auto one = std::make_pair(dz, std::make_pair(dy, dx)), other = std::make_pair(oz, std::make_pair(oy, ox));
+          if (one < other) continue;
+          const int times = one == other ? 1 : 2;
+          disp.push_back(tiles ? make_int4(dy * (L + 2 * halo) + dx, r2, times, 0) : make_int4(dx, dy, dz, 2 * r2 + times - 1));
+        }
     }
+    start.push_back((int)disp.size());
+    if (tiles)
+      for (size_t k = 0; k + 1 < start.size(); ++k) {
+        const auto key = [](const int4 &v) { return std::make_pair(v.y, v.z); };
+        std::sort(disp.begin() + start[k], disp.begin() + start[k + 1], [&](const int4 &u, const int4 &v) { return key(u) < key(v); });
+        for (int q = start[k]; q < start[k + 1]; ++q) disp[(size_t)q].w = q + 1 == start[k + 1] || key(disp[(size_t)q]) != key(disp[(size_t)q + 1]);
+      }
     DeviceGuard dg(s->device);
-    int4 *d_disp = nullptr;
-    unsigned long long *d_out = nullptr;
+    int4 *d_disp = nullptr;   // displacements, then the starts
     const size_t shells = (size_t)r2_max + 1;
-    hipError_t e = dalloc(&d_disp, disp.size() * sizeof(int4));
-    if (e == hipSuccess) e = dalloc(&d_out, 2 * shells * sizeof(unsigned long long));
-    if (e == hipSuccess) e = hipMemcpyAsync(d_disp, disp.data(), disp.size() * sizeof(int4), hipMemcpyHostToDevice, s->stream);
+    const size_t disp_bytes = disp.size() * sizeof(int4);
+    hipError_t e = ensure_obs_buffers(s, (2 * shells + 3u * (size_t)s->R - 1) / (3u * (size_t)s->R));
+    unsigned long long *d_out = s->counts;
+    if (e == hipSuccess) e = dalloc(&d_disp, disp_bytes + start.size() * sizeof(int));
+    int *d_start = reinterpret_cast<int *>(d_disp + disp.size());
+    if (e == hipSuccess) e = hipMemcpyAsync(d_disp, disp.data(), disp_bytes, hipMemcpyHostToDevice, s->stream);
+    if (e == hipSuccess) e = hipMemcpyAsync(d_start, start.data(), start.size() * sizeof(int), hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess) e = hipMemsetAsync(d_out, 0, 2 * shells * sizeof(unsigned long long), s->stream);
     if (e == hipSuccess) {
       ka::PairArgs a{};
@@ -1668,16 +1689,18 @@ extern "C" int ka_observe_pairs(ka_sim *s, int r2_max, int64_t *S2, int64_t *S11
       a.planes = s->planes;
       a.disp = d_disp;
       a.n_disp = (int)disp.size();
+      a.start = d_start;
+      a.halo = halo;
+      a.rows = rows;
       a.r2_max = r2_max;
       a.S2 = d_out;
       a.S11 = d_out + shells;
-      e = ka::launch_pairs(a, s->wpt, s->stream);
+      e = tiles ? ka::launch_pairs_tile(a, s->wpt, words, s->stream) : ka::launch_pairs(a, s->wpt, s->stream);
     }
     std::vector<unsigned long long> host(2 * shells);
     if (e == hipSuccess) e = hipMemcpyAsync(host.data(), d_out, 2 * shells * sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
     (void)hipFree(d_disp);
-    (void)hipFree(d_out);
     if (e != hipSuccess) return hip_fail(e, "ka_observe_pairs");
     for (size_t q = 0; q < shells; ++q) {
       if (S2) S2[q] = (int64_t)host[q];

@@ -209,13 +209,22 @@ struct PairArgs {
   const u64 *n0;
   LatticeGeom g;
   int planes;
-  const int4 *disp;                    // (dx, dy, dz, r2)
+  // one of every displacement and its opposite.  launch_pairs: (dx, dy, dz, 2 * r2 + 1 if it counts
+  // twice); launch_pairs_tile: (offset in the tile, r2, times it counts, 1 if the next one differs
+  // in r2 or times), those with dz from start[dz] to start[dz + 1], ordered by r2 and times
+  const int4 *disp;
   int n_disp;
+  const int *start;
+  int halo;                            // tiles: largest component, at most L / 2
+  int rows;                            // tiles: rows of a workgroup
   int r2_max;
   unsigned long long *S2;              // [r2_max + 1]
   unsigned long long *S11;
 };
 hipError_t launch_pairs(const PairArgs &a, int wpt, hipStream_t s);
+// Rows and words at a time of the tile kernel; false if the halo's tile does not fit in LDS.
+bool pairs_tile_rows(int L, int halo, int r2_max, int *rows, int *words);
+hipError_t launch_pairs_tile(const PairArgs &a, int wpt, int words, hipStream_t s);
 // Graphs without a geometry: out[0] += sum_i Q_i, out[1] += sum_i Q_i^2 with Q_i the number
 // of replicas b with n_i^b(t) n_i^b(0) = 1.
 struct PairGraphArgs {

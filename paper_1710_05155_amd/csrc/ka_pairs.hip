@@ -7,9 +7,14 @@
 //     S2[r2]  += popcount(Q_i & Q_{i+delta})            summed over sites i and words,
 //     S11[r2] += popcount(Q_i) * popcount(Q_{i+delta})  with popcounts over all words,
 // i.e. the replica sums of q_i q_j and the products of the replica sums, over ordered pairs.
-// One thread per site holds its Q words in registers; a workgroup takes a chunk of
-// displacements, reduces each one over the wave with shuffles and adds it into 64-bit LDS
-// shell accumulators, which go to global memory once per workgroup.
+// Both sums are the same for delta and -delta, so only one of the two is computed and counts twice.
+//
+// k_pairs_tile: a workgroup takes some rows of one plane, with the Q words and replica sums of the
+// plane dz above (their halo included) in LDS; for every displacement with that dz a thread ANDs
+// its sites' Q, held in registers, with the words at one offset from them.  k_pairs, one thread
+// per site gathering from global memory, covers radii whose halo does not fit in LDS.
+#include <algorithm>
+
 #include "ka_device.h"
 
 namespace ka {
@@ -20,6 +25,8 @@ using namespace dev;
 constexpr int kPairBlock = 256;
 constexpr int kPairChunk = 32;     // displacements per workgroup
 constexpr int kMaxWords = 16;      // up to 1024 replicas
+constexpr int kTileBlock = 512, kTileSites = 2;   // threads of k_pairs_tile, sites per thread
+constexpr size_t kTileLds = 80 << 10;   // two workgroups to a CU
 
 __device__ __forceinline__ unsigned wave_sum(unsigned v)
 {
@@ -75,7 +82,9 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a)
   const int d0 = (int)blockIdx.y * kPairChunk;
   const int d1 = min(a.n_disp, d0 + kPairChunk);
   for (int dq = d0; dq < d1; ++dq) {
-    const int4 dv = a.disp[dq];
+    const int4 dv = a.disp[dq];   // components, shell * 2 + whether it counts twice
+    const int r2 = dv.w >> 1;
+    const u64 times = 1u + (unsigned)(dv.w & 1);
     int y[3] = {x[0] + dv.x, x[1] + dv.y, x[2] + dv.z};
     for (int k = 0; k < a.g.d; ++k) {
       if (y[k] < 0) y[k] += a.g.L;
@@ -98,8 +107,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a)
     c2 = wave_sum(c2);
     c11 = wave_sum(c11);
     if (__lane_id() == 0) {
-      atomicAdd(&acc2[dv.w], (unsigned long long)c2);
-      atomicAdd(&acc11[dv.w], (unsigned long long)c11);
+      atomicAdd(&acc2[r2], (u64)c2 * times);
+      atomicAdd(&acc11[r2], (u64)c11 * times);
     }
   }
   __syncthreads();
@@ -107,6 +116,147 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a)
     if (acc2[q]) atomicAdd(&a.S2[q], acc2[q]);
     if (acc11[q]) atomicAdd(&a.S11[q], acc11[q]);
   }
+}
+
+// Sum over the wave, on lane 63: adds of lanes 1, 2, 4 and 8 below within rows of 16, then of the
+// last lane of the row and of the two rows before.
+__device__ __forceinline__ unsigned wave_sum_last(unsigned v)
+{
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);   // row_shr:2
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);   // row_shr:4
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);   // row_shr:8
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  v += (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+
+// Word w of q at element e.
+__device__ __forceinline__ u64 site_word(const PairArgs &a, int wpt, int e, int w)
+{
+  const size_t at = ((size_t)(w / wpt) * (size_t)a.g.N + (size_t)e) * (size_t)wpt + (size_t)(w % wpt);
+  return a.n[at] & a.n0[at];
+}
+
+// Bound by VALU and LDS: per site, displacement and word two ANDs, two population counts and an 8
+// byte LDS read.  WC words at a time (S11 comes with the first of them).
+template <int WC>
+__global__ __launch_bounds__(kTileBlock) void k_pairs_tile(PairArgs a, int wpt)
+{
+  extern __shared__ u64 pair_lds[];
+  const int tid = (int)threadIdx.x;
+  const int L = a.g.L, h = a.halo, T = a.rows;
+  const int width = L + 2 * h, area = (T + 2 * h) * width;
+  // word pairs in one 16-byte read (WC = 1: single words)
+  constexpr int V = WC > 1 ? 2 : 1, G = WC / V;
+  u64 *q = pair_lds;                                                  // [G][area][V]
+  u64 *acc2 = q + (size_t)WC * area, *acc11 = acc2 + a.r2_max + 1;
+  unsigned short *sum = reinterpret_cast<unsigned short *>(acc11 + a.r2_max + 1);   // [area]
+  const int y0 = (int)blockIdx.x * T, z = (int)blockIdx.y, dz = (int)blockIdx.z;
+  const int zb = z + dz < L ? z + dz : z + dz - L;
+  const int d0 = a.start[dz], d1 = a.start[dz + 1];
+  if (d0 == d1) return;
+  for (int k = tid; k <= a.r2_max; k += kTileBlock) acc2[k] = acc11[k] = 0;
+  // this thread's sites: tile positions tid + k * kTileBlock (rows beyond the lattice hold none)
+  const int W = a.planes * wpt;
+  int at[kTileSites], elem[kTileSites];
+  unsigned p[kTileSites];
+#pragma unroll
+  for (int k = 0; k < kTileSites; ++k) {
+    const int s = tid + k * kTileBlock, y = s / L, x = s - y * L;
+    const bool valid = y < T && y0 + y < L;
+    const int xyz[3] = {x, valid ? y0 + y : 0, z};
+    elem[k] = valid ? element_of(a.g, xyz) : -1;
+    at[k] = valid ? (y + h) * width + x + h : h * width + h;
+    p[k] = 0;
+  }
+  const float inv = 1.0f / (float)width;
+  constexpr int U = 4;   // tile sites a thread loads at a time
+  for (int w0 = 0; w0 < W; w0 += WC) {
+    __syncthreads();   // the previous words' reads are done
+    for (int k0 = tid; k0 < area; k0 += U * kTileBlock) {
+      u64 v[U][WC];
+      int e[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(k0 + u * kTileBlock, area - 1);
+        int y = (int)((float)k * inv);   // k below 2^14: exact after one correction
+        y -= y * width > k;
+        y += (y + 1) * width <= k;
+        int x = k - y * width - h;
+        y += y0 - h;
+        x = x < 0 ? x + L : x >= L ? x - L : x;
+        y = y < 0 ? y + L : y >= 2 * L ? y - 2 * L : y >= L ? y - L : y;
+        const int xyz[3] = {x, y, zb};
+        e[u] = element_of(a.g, xyz);
+#pragma unroll
+        for (int w = 0; w < WC; ++w) v[u][w] = w0 + w < W ? site_word(a, wpt, e[u], w0 + w) : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int k = min(k0 + u * kTileBlock, area - 1);   // (the last site more than once, with the same words)
+        unsigned sites = 0;
+#pragma unroll
+        for (int w = 0; w < WC; ++w) {
+          q[((w / V) * area + k) * V + w % V] = v[u][w];
+          sites += (unsigned)__popcll(v[u][w]);
+        }
+        if (w0 == 0) {   // replica sum: the words that are here, and the others
+          for (int w = WC; w < W; ++w) sites += (unsigned)__popcll(site_word(a, wpt, e[u], w));
+          sum[k] = (unsigned short)sites;
+        }
+      }
+    }
+    u64 qi[kTileSites][WC];
+#pragma unroll
+    for (int k = 0; k < kTileSites; ++k) {
+#pragma unroll
+      for (int w = 0; w < WC; ++w) {
+        qi[k][w] = elem[k] >= 0 && w0 + w < W ? site_word(a, wpt, elem[k], w0 + w) : 0;
+        if (w0 == 0) p[k] += (unsigned)__popcll(qi[k][w]);
+      }
+      if (w0 == 0 && elem[k] >= 0)
+        for (int w = WC; w < W; ++w) p[k] += (unsigned)__popcll(site_word(a, wpt, elem[k], w));
+    }
+    __syncthreads();
+    // Displacements of one shell follow each other, and are summed over the wave together (at
+    // most 16 of them: a product of replica sums takes 2^27 over a wave).
+    unsigned c2 = 0, c11 = 0;
+    for (int d = d0, run = 1; d < d1; ++d, ++run) {
+      const int4 dv = a.disp[d];   // offset in the tile, shell, how often it counts, whether the next one differs in these
+#pragma unroll
+      for (int k = 0; k < kTileSites; ++k) {
+        const int j = at[k] + dv.x;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          const Elem<V> x = ld<V>(q + (size_t)g * area * V, j);
+#pragma unroll
+          for (int w = 0; w < V; ++w) c2 += (unsigned)__popcll(qi[k][g * V + w] & x.w[w]);
+        }
+        if (w0 == 0) c11 += p[k] * (unsigned)sum[j];
+      }
+      if (!dv.w && run < 16) continue;
+      c2 = wave_sum_last(c2);
+      if (w0 == 0) c11 = wave_sum_last(c11);
+      if (__lane_id() == 63) {
+        if (c2) atomicAdd(&acc2[dv.y], (u64)c2 * (u64)dv.z);
+        if (w0 == 0 && c11) atomicAdd(&acc11[dv.y], (u64)c11 * (u64)dv.z);
+      }
+      c2 = c11 = 0;
+      run = 0;
+    }
+  }
+  __syncthreads();
+  for (int k = tid; k <= a.r2_max; k += kTileBlock) {
+    if (acc2[k]) atomicAdd(&a.S2[k], acc2[k]);
+    if (acc11[k]) atomicAdd(&a.S11[k], acc11[k]);
+  }
+}
+
+size_t tile_lds(int L, int halo, int rows, int r2_max, int wc)
+{
+  const size_t area = (size_t)(rows + 2 * halo) * (size_t)(L + 2 * halo);
+  return area * (size_t)(8 * wc + 2) + (size_t)(r2_max + 1) * 16u + 16u;
 }
 
 // Graphs without a geometry (Sec. 3.3: distance 0 for i = j, 1 otherwise): only the per-site
@@ -143,6 +293,38 @@ hipError_t launch_pairs_graph(const PairGraphArgs &a, int wpt, hipStream_t s)
     hipLaunchKernelGGL((k_pairs_graph<2>), grid, dim3(kPairBlock), 0, s, a);
   else
     hipLaunchKernelGGL((k_pairs_graph<1>), grid, dim3(kPairBlock), 0, s, a);
+  return hipGetLastError();
+}
+
+bool pairs_tile_rows(int L, int halo, int r2_max, int *rows, int *words)
+{
+  if (L > kTileSites * kTileBlock) return false;
+  const int T = std::min(L, kTileSites * kTileBlock / L);
+  for (int wc = 4; wc >= 1; wc /= 2)
+    if (tile_lds(L, halo, T, r2_max, wc) <= kTileLds) {
+      *rows = T;
+      *words = wc;
+      return true;
+    }
+  return false;
+}
+
+hipError_t launch_pairs_tile(const PairArgs &a, int wpt, int words, hipStream_t s)
+{
+  const size_t lds = tile_lds(a.g.L, a.halo, a.rows, a.r2_max, words);
+  if (a.rows < 1 || a.rows * a.g.L > kTileSites * kTileBlock || 2 * a.halo > a.g.L || lds > kTileLds) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((a.g.L + a.rows - 1) / a.rows), (unsigned)(a.g.d == 3 ? a.g.L : 1), (unsigned)(a.g.d == 3 ? a.halo + 1 : 1));
+#define KA_PT(WC)                                                                                        \
+  do {                                                                                                   \
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_pairs_tile<WC>),           \
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTileLds); \
+    if (e != hipSuccess) return e;                                                                       \
+    hipLaunchKernelGGL((k_pairs_tile<WC>), grid, dim3(kTileBlock), lds, s, a, wpt);                      \
+  } while (0)
+  if (words == 4) KA_PT(4);
+  else if (words == 2) KA_PT(2);
+  else KA_PT(1);
+#undef KA_PT
   return hipGetLastError();
 }
 
