@@ -13,6 +13,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <utility>
 #include <vector>
 
@@ -523,21 +524,6 @@ template <typename T>
 hipError_t dalloc(T **p, size_t bytes)
 {
   return hipMalloc(reinterpret_cast<void **>(p), bytes ? bytes : 16);
-}
-
-// Element index of canonical site i in the lattice device layout.
-inline int64_t lattice_element(const ka::LatticeGeom &g, int64_t i)
-{
-  int64_t sub = 0, pos = 0, sm = 1, pm = 1;
-  for (int k = 0; k < g.d; ++k) {
-    const int x = (int)(i % g.L);
-    i /= g.L;
-    sub += (x & 3) * sm;
-    pos += (x >> 2) * pm;
-    sm *= 4;
-    pm *= g.Q;
-  }
-  return sub * g.P + pos;
 }
 
 struct DeviceGuard {
@@ -1711,6 +1697,99 @@ extern "C" int ka_observe_pairs(ka_sim *s, int r2_max, int64_t *S2, int64_t *S11
   });
 }
 
+namespace {
+
+// Staging of state copies: kept with the sim up to 2^15 words (256 KiB, in the observation buffer),
+// otherwise allocated for the call, 2^22 words (32 MiB) at most.
+constexpr int64_t kStateKept = 1 << 15, kStateStaging = 1 << 22;
+
+struct StateStaging {
+  u64 *words = nullptr;
+  int64_t size = 0;
+  bool own = false;
+  ~StateStaging()
+  {
+    if (own) (void)hipFree(words);
+  }
+  hipError_t get(ka_sim *s, int64_t need)
+  {
+    if (need > kStateKept) {
+      size = std::min(need, kStateStaging);
+      own = dalloc(&words, (size_t)size * 8) == hipSuccess;
+      if (own) return hipSuccess;
+      (void)hipGetLastError();   // little memory left: smaller pieces
+    }
+    size = std::min(need, kStateKept);
+    const size_t row = 3u * (size_t)s->R;
+    const hipError_t e = ensure_obs_buffers(s, ((size_t)size + row - 1) / row);
+    words = reinterpret_cast<u64 *>(s->counts);
+    return e;
+  }
+};
+
+// The canonical words of one state array, out to host memory or in from it, a staging buffer at
+// a time (the copies to and from the caller's pageable memory return when they are done).
+hipError_t move_state(ka_sim *s, const StateStaging &st, u64 *state, uint64_t *host, bool out)
+{
+  ka::StateArgs a{};
+  a.state = state;
+  a.staging = st.words;
+  a.site_of = s->lattice ? nullptr : s->site_of;
+  a.g = s->geom;
+  a.N = (int)s->N;
+  a.wpt = s->wpt;
+  const int64_t words = s->N * s->W;
+  hipError_t e = hipSuccess;
+  for (a.t0 = 0; a.t0 < words && e == hipSuccess; a.t0 = a.t1) {
+    a.t1 = std::min(words, a.t0 + st.size);
+    const size_t bytes = (size_t)(a.t1 - a.t0) * 8;
+    if (out) {
+      e = ka::launch_state(a, true, s->stream);
+      if (e == hipSuccess) e = hipMemcpyAsync(host + a.t0, st.words, bytes, hipMemcpyDeviceToHost, s->stream);
+    } else {
+      e = hipMemcpyAsync(st.words, host + a.t0, bytes, hipMemcpyHostToDevice, s->stream);
+      if (e == hipSuccess) e = ka::launch_state(a, false, s->stream);
+    }
+    if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+  }
+  return e;
+}
+
+// Touches the pages of arrays that are about to be written whole, so that a large export is
+// not bound by their first use on one thread (fresh memory is copied to at 4 GB/s, touched memory
+// at 17).  Ends with the object.
+class PageToucher {
+ public:
+  void add(uint64_t *p, size_t bytes)
+  {
+    constexpr size_t kWorth = (size_t)4 << 20;
+    constexpr int kThreads = 4;
+    if (!p || bytes < kWorth) return;
+    char *base = reinterpret_cast<char *>(p);
+    for (int k = 0; k < kThreads; ++k) {
+      const size_t a = bytes / kThreads * k, b = k + 1 < kThreads ? bytes / kThreads * (k + 1) : bytes;
+      try {
+        threads_.emplace_back([base, a, b] {
+          for (size_t q = a; q < b; q += 4096) *reinterpret_cast<volatile char *>(base + q) = 0;
+        });
+      } catch (...) {
+        return;   // no more threads: the copy touches the rest itself
+      }
+    }
+  }
+  void wait()
+  {
+    for (std::thread &t : threads_) t.join();
+    threads_.clear();
+  }
+  ~PageToucher() { wait(); }
+
+ private:
+  std::vector<std::thread> threads_;
+};
+
+}  // namespace
+
 extern "C" int ka_get_state(ka_sim *s, uint64_t *n, uint64_t *n0, uint64_t *f, int64_t *t)
 {
   return ka_guard([&]() -> int {
@@ -1718,24 +1797,25 @@ extern "C" int ka_get_state(ka_sim *s, uint64_t *n, uint64_t *n0, uint64_t *f, i
     if (rc) return rc;
     DeviceGuard dg(s->device);
     const size_t words = (size_t)s->N * s->W;
-    std::vector<u64> buf(words);
     uint64_t *outs[3] = {n, n0, f};
     u64 *srcs[3] = {s->n, s->n0, s->f};
     hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "ka_get_state");
     rc = check_init_flag(s);
     if (rc) return rc;
+    StateStaging st;
+    if (n || n0 || f) {
+      e = st.get(s, (int64_t)words);
+      if (e != hipSuccess) return fail(KA_ENOMEM, "state staging: %s", hipGetErrorString(e));
+    }
+    PageToucher touch[3];   // of the next array while one is copied
+    touch[0].add(outs[0], words * 8);
     for (int k = 0; k < 3; ++k) {
+      touch[k].wait();
+      if (k < 2) touch[k + 1].add(outs[k + 1], words * 8);
       if (!outs[k]) continue;
-      e = hipMemcpyAsync(buf.data(), srcs[k], words * 8, hipMemcpyDeviceToHost, s->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+      e = move_state(s, st, srcs[k], outs[k], true);
       if (e != hipSuccess) return hip_fail(e, "ka_get_state copy");
-      for (int64_t i = 0; i < s->N; ++i) {
-        const int64_t el = s->lattice ? lattice_element(s->geom, i) : s->plan->label[(size_t)i];
-        for (int p = 0; p < s->planes; ++p)
-          for (int w = 0; w < s->wpt; ++w)
-            outs[k][(size_t)(p * s->wpt + w) * s->N + i] = buf[((size_t)p * s->N + el) * s->wpt + w];
-      }
     }
     if (t) *t = s->t;
     return KA_OK;
@@ -1751,21 +1831,15 @@ extern "C" int ka_set_state(ka_sim *s, const uint64_t *n, const uint64_t *n0, co
     if (!n || !n0 || !f) return fail(KA_EINVAL, "ka_set_state needs n, n0 and f");
     if (t < 0 || t >= (1ll << 32)) return fail(KA_EINVAL, "t out of range");
     DeviceGuard dg(s->device);
-    const size_t words = (size_t)s->N * s->W;
-    std::vector<u64> buf(words);
     const uint64_t *ins[3] = {n, n0, f};
     u64 *dsts[3] = {s->n, s->n0, s->f};
     hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "ka_set_state");
+    StateStaging st;
+    e = st.get(s, s->N * s->W);
+    if (e != hipSuccess) return fail(KA_ENOMEM, "state staging: %s", hipGetErrorString(e));
     for (int k = 0; k < 3; ++k) {
-      for (int64_t i = 0; i < s->N; ++i) {
-        const int64_t el = s->lattice ? lattice_element(s->geom, i) : s->plan->label[(size_t)i];
-        for (int p = 0; p < s->planes; ++p)
-          for (int w = 0; w < s->wpt; ++w)
-            buf[((size_t)p * s->N + el) * s->wpt + w] = ins[k][(size_t)(p * s->wpt + w) * s->N + i];
-      }
-      e = hipMemcpyAsync(dsts[k], buf.data(), words * 8, hipMemcpyHostToDevice, s->stream);
-      if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
+      e = move_state(s, st, dsts[k], const_cast<uint64_t *>(ins[k]), false);
       if (e != hipSuccess) return hip_fail(e, "ka_set_state copy");
     }
     // the new f may have fewer bits: forget which elements were known to be full

@@ -202,6 +202,17 @@ bool lds_graph_accept_supported(int z, int wpt);
 // Acceptance words of a.n_sweeps sweeps for the LDS sweep, into a.acc.
 hipError_t launch_lds_accept(const SweepLds &a, bool lattice, int wpt, hipStream_t s);
 
+// Canonical words [t0, t1) of one state array to (out) or from a staging buffer (ka_state.hip).
+struct StateArgs {
+  u64 *state;                // [planes][N][wpt], device order
+  u64 *staging;              // [t1 - t0]
+  const int32_t *site_of;    // general graphs: canonical vertex of each device index (lattices: null)
+  LatticeGeom g;
+  int N, wpt;
+  int64_t t0, t1;
+};
+hipError_t launch_state(const StateArgs &a, bool out, hipStream_t s);
+
 // Spatial four-point sums (ka_pairs.hip).
 constexpr int kMaxPairShells = 2049;   // r2_max <= 2048
 struct PairArgs {
