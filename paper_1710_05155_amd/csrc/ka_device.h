@@ -411,8 +411,10 @@ __device__ __forceinline__ void moved_ever_or(u64 *fb, int i, const u64 (&d)[WPT
 // The exchange across one edge (i, j) on the plane at base nb (moved-ever words at fb;
 // global memory or LDS), given the element indices of i, j and of their K neighbours other
 // than the partner; draw(r) supplies the edge's acceptance words once the state loads are
-// issued.  Shared by every path.
-template <int K, int WPT, typename Draw, typename SatT = NoSat>
+// issued.  Shared by every path.  EARLY: the moved-ever words are loaded with the state words,
+// not after the exchange is known to happen, which saves a dependent load where a pass is bound
+// by latency and costs bytes where it is bound by them.
+template <int K, int WPT, bool EARLY = false, typename Draw, typename SatT = NoSat>
 __device__ __forceinline__ void edge_update_with(u64 *nb, u64 *fb, int i, int j, const int (&ii)[K],
                                                  const int (&jj)[K], int m, Draw draw, SatT sat = SatT{})
 {
@@ -431,6 +433,12 @@ __device__ __forceinline__ void edge_update_with(u64 *nb, u64 *fb, int i, int j,
     full_i = (sat.bits[bi >> 5] >> (bi & 31u)) & 1u;
     full_j = (sat.bits[bj >> 5] >> (bj & 31u)) & 1u;
   }
+  Elem<WPT> fi, fj;
+  if constexpr (EARLY) {
+    static_assert(std::is_same_v<SatT, NoSat>, "a saturation bitmap decides the loads first");
+    fi = ld<WPT>(fb, i);
+    fj = ld<WPT>(fb, j);
+  }
   u64 r[WPT];
   draw(r);
   u64 d[WPT];
@@ -444,9 +452,10 @@ __device__ __forceinline__ void edge_update_with(u64 *nb, u64 *fb, int i, int j,
     // f only gains a bit the first time a site changes in a replica, so it is stored
     // only then: over a run a word is rewritten at most 64 times.  Both loads are issued
     // before either is used.
-    Elem<WPT> fi, fj;
-    if (!full_i) fi = ld<WPT>(fb, i);
-    if (!full_j) fj = ld<WPT>(fb, j);
+    if constexpr (!EARLY) {
+      if (!full_i) fi = ld<WPT>(fb, i);
+      if (!full_j) fj = ld<WPT>(fb, j);
+    }
     if (!full_i) moved_ever_or<WPT>(fb, i, d, fi, sat);
     if (!full_j) moved_ever_or<WPT>(fb, j, d, fj, sat);
   }
@@ -454,13 +463,13 @@ __device__ __forceinline__ void edge_update_with(u64 *nb, u64 *fb, int i, int j,
 
 // The same exchange for the edge with canonical id e, class c, sweep t: its acceptance words
 // are drawn here.
-template <int K, int WPT, typename SatT = NoSat>
+template <int K, int WPT, bool EARLY = false, typename SatT = NoSat>
 __device__ __forceinline__ void edge_update(u64 *nb, u64 *fb, int i, int j, const int (&ii)[K],
                                             const int (&jj)[K], uint32_t e, int plane, int m,
                                             uint32_t t, uint32_t c, uint32_t k0, uint32_t k1,
                                             int noise, SatT sat = SatT{})
 {
-  edge_update_with<K, WPT>(nb, fb, i, j, ii, jj, m, [&](u64 (&r)[WPT]) {
+  edge_update_with<K, WPT, EARLY>(nb, fb, i, j, ii, jj, m, [&](u64 (&r)[WPT]) {
     accept_words<WPT>(t, c, e, plane, k0, k1, noise, r);
   }, sat);
 }
@@ -480,7 +489,7 @@ __device__ __forceinline__ void lattice_edge_indices(const LatticeGeom &g, const
 }
 
 // One lattice edge (si, si + e_MU), with si already decoded.
-template <int D, int MU, int WPT>
+template <int D, int MU, int WPT, bool EARLY = false>
 __device__ __forceinline__ void lattice_edge_at(u64 *nb, u64 *fb, const LatticeGeom &g,
                                                 const Site &si, int plane, int m, uint32_t t,
                                                 uint32_t c, uint32_t k0, uint32_t k1, int noise)
@@ -489,16 +498,16 @@ __device__ __forceinline__ void lattice_edge_at(u64 *nb, u64 *fb, const LatticeG
   int i, j, ii[K], jj[K];
   uint32_t e;
   lattice_edge_indices<D, MU>(g, si, i, j, ii, jj, e);
-  edge_update<K, WPT>(nb, fb, i, j, ii, jj, e, plane, m, t, c, k0, k1, noise);
+  edge_update<K, WPT, EARLY>(nb, fb, i, j, ii, jj, e, plane, m, t, c, k0, k1, noise);
 }
 
 // The same edge given by its sublattice and position.
-template <int D, int MU, int WPT>
+template <int D, int MU, int WPT, bool EARLY = false>
 __device__ __forceinline__ void lattice_edge(u64 *nb, u64 *fb, const LatticeGeom &g, int sub,
                                              int pos, int plane, int m, uint32_t t, uint32_t c,
                                              uint32_t k0, uint32_t k1, int noise)
 {
-  lattice_edge_at<D, MU, WPT>(nb, fb, g, decode(g, D, sub, pos), plane, m, t, c, k0, k1, noise);
+  lattice_edge_at<D, MU, WPT, EARLY>(nb, fb, g, decode(g, D, sub, pos), plane, m, t, c, k0, k1, noise);
 }
 
 // One general-graph edge: entry k of the class-sorted edge list, record (u, v, e, 0) and

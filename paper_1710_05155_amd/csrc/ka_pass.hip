@@ -26,6 +26,15 @@ constexpr int kObsBlocks = 512, kObsPlaneBlocks = 256, kObsSpread = 80;
 constexpr int kGraphSmallBlock = 64;
 constexpr long long kGraphSmallEdges = 65536;
 
+// Lattice passes of at most this many edge-words (edges of a class x words of the launch) load
+// the moved-ever words together with the state words.  Up to there a pass is bound by its chain
+// of dependent loads, and the words come from the caches; above, by bytes, and at low mobility
+// most edges exchange nothing and need neither word.  Microseconds per class, loaded late -> with
+// the state, 64 replicas: L = 48 3.49 -> 3.32 at density 0.8, L = 64 3.57 -> 3.41, L = 128 (2^19
+// edge-words) 7.62 -> 7.52 and 6.57 -> 6.32 at density 0.9; 256 replicas, L = 64 (2^18) 4.48 ->
+// 4.36, but L = 128 (2^21) 22.4 -> 22.3 and, at density 0.9, 15.1 -> 17.1.
+constexpr long long kEarlyEdges = 1 << 19;
+
 // ------------------------------------------------------------------------------------
 // Global-memory class pass kernels: one launch per (class, sweep) over a range of planes.
 // ------------------------------------------------------------------------------------
@@ -33,7 +42,7 @@ constexpr long long kGraphSmallEdges = 65536;
 // (coalesced 64 x 16 B loads); consecutive waves cover the class's other lower-endpoint
 // sublattices at the same positions, so the neighbour sublattices they share are fetched
 // once and then served from L2 (together with the XCD-contiguous block order).
-template <int D, int MU, int WPT>
+template <int D, int MU, int WPT, bool EARLY>
 __global__ __launch_bounds__(kPassBlock) void k_pass_lattice(PassLattice a, int m)
 {
   const int lin = xcd_remap(blockIdx.x, gridDim.x);
@@ -64,8 +73,8 @@ __global__ __launch_bounds__(kPassBlock) void k_pass_lattice(PassLattice a, int 
   if (pos >= a.g.P) return;
   const int sub = class_sublattice(D, MU, (int)(a.c & 3u), q);
   const size_t off = (size_t)plane * (size_t)a.g.N * WPT;
-  lattice_edge<D, MU, WPT>(a.n + off, a.f + off, a.g, sub, pos, plane, m, a.t, a.c,
-                           a.key0, a.key1, a.noise);
+  lattice_edge<D, MU, WPT, EARLY>(a.n + off, a.f + off, a.g, sub, pos, plane, m, a.t, a.c,
+                                  a.key0, a.key1, a.noise);
 }
 
 template <int Z, int WPT, int BLOCK>
@@ -133,8 +142,14 @@ hipError_t launch_pass_lattice(const PassLattice &a, int m, int wpt, hipStream_t
 {
   const dim3 grid((unsigned)(a.blocks_per_plane * a.planes));
   const dim3 block(kPassBlock);
-#define KA_LAT(D, MU, W) \
-  hipLaunchKernelGGL((k_pass_lattice<D, MU, W>), grid, block, 0, s, a, m)
+  const bool early = (long long)a.g.N / 4 * a.planes * wpt <= kEarlyEdges;
+#define KA_LAT(D, MU, W)                                                                   \
+  do {                                                                                     \
+    if (early)                                                                             \
+      hipLaunchKernelGGL((k_pass_lattice<D, MU, W, true>), grid, block, 0, s, a, m);       \
+    else                                                                                   \
+      hipLaunchKernelGGL((k_pass_lattice<D, MU, W, false>), grid, block, 0, s, a, m);      \
+  } while (0)
   if (a.g.d == 2) {
     if (wpt == 2) {
       if (a.mu == 0) KA_LAT(2, 0, 2); else KA_LAT(2, 1, 2);
