@@ -495,9 +495,10 @@ size_t graph_device_bytes(const ka_graph *g)
 
 void free_device(ka_sim *s)
 {
-  (void)hipFree(s->n);
-  (void)hipFree(s->n0);
-  (void)hipFree(s->f);
+  for (ka::u64 *&p : s->state_mem) {
+    (void)hipFree(p);
+    p = nullptr;
+  }
   (void)hipFree(s->nbr);
   (void)hipFree(s->edges);
   (void)hipFree(s->class_start_d);
@@ -515,15 +516,49 @@ void free_device(ka_sim *s)
   (void)hipFree(s->lds_snap);
   s->lds_snap = nullptr;
   s->lds_snap_rows = 0;
-  (void)hipFree(s->n_next);
-  s->n_next = nullptr;
-  s->n = s->n0 = s->f = nullptr;
+  s->n = s->n0 = s->f = s->n_next = nullptr;
 }
 
 template <typename T>
 hipError_t dalloc(T **p, size_t bytes)
 {
   return hipMalloc(reinterpret_cast<void **>(p), bytes ? bytes : 16);
+}
+
+// n, n0 and f, in one allocation: above 1 MiB every hipMalloc and hipFree pair maps and unmaps
+// its pages (25 us up to 64 MiB; beyond what the runtime keeps, three of 64 MiB take 570 us and
+// one of 192 MiB 295), which is a good part of a short job.  Host time of ka_init and ka_free
+// together, three allocations -> one: 2D L = 512 x 64 126 -> 37 us, 3D L = 128 x 64 110 -> 36,
+// x 256 794 -> 330.  Where the one allocation is refused (a runtime may cap its size), three are
+// tried.
+hipError_t alloc_state(ka_sim *s)
+{
+  const size_t bytes = (size_t)s->N * (size_t)s->W * 8u;
+  const size_t part = (bytes + 4095) / 4096 * 4096;
+  if (dalloc(&s->state_mem[0], 2 * part + bytes) == hipSuccess) {
+    s->n = s->state_mem[0];
+    s->n0 = s->n + part / 8;
+    s->f = s->n0 + part / 8;
+    return hipSuccess;
+  }
+  (void)hipGetLastError();
+  s->state_mem[0] = nullptr;
+  hipError_t e = hipSuccess;
+  for (int q = 0; q < 3 && e == hipSuccess; ++q) e = dalloc(&s->state_mem[q], bytes);
+  s->n = s->state_mem[0];
+  s->n0 = s->state_mem[1];
+  s->f = s->state_mem[2];
+  return e;
+}
+
+// The second copy of n of a large 2D lattice, on its first sweep that uses it.
+hipError_t ensure_n_next(ka_sim *s)
+{
+  if (s->n_next) return hipSuccess;
+  const hipError_t e = dalloc(&s->state_mem[3], (size_t)s->N * (size_t)s->W * 8u);
+  if (e != hipSuccess) s->state_mem[3] = nullptr;
+  s->n_next = s->state_mem[3];
+  return e;
 }
 
 struct DeviceGuard {
@@ -998,12 +1033,9 @@ hipError_t launch_resident(ka_sim *s, int64_t t_from, int64_t t_to, int q0, int 
 // n sweeps of a large 2D lattice, one to three a launch, between the two copies of n.
 hipError_t sweep_tiles(ka_sim *s, int64_t n)
 {
-  if (!s->n_next) {
-    const hipError_t e = dalloc(&s->n_next, (size_t)s->N * (size_t)s->W * 8u);
-    if (e != hipSuccess) return e;
-  }
+  hipError_t e = ensure_n_next(s);
+  if (e != hipSuccess) return e;
   const int64_t chunk = lds_chunk(s);
-  hipError_t e = hipSuccess;
   for (int64_t done = 0; done < n && e == hipSuccess;) {
     const int64_t k = std::min(chunk, n - done);
     if (s->lds_acc) e = ka::launch_square_accept(square_args(s, s->t + done, k), s->stream);
@@ -1027,9 +1059,8 @@ hipError_t sweep_tiles(ka_sim *s, int64_t n)
 Route sweep_route(ka_sim *s)
 {
   const Route by = route(s);
-  if (by == Route::tiles && !s->n_next && dalloc(&s->n_next, (size_t)s->N * (size_t)s->W * 8u) != hipSuccess) {
+  if (by == Route::tiles && ensure_n_next(s) != hipSuccess) {
     (void)hipGetLastError();
-    s->n_next = nullptr;
     return Route::passes;
   }
   return by;
@@ -1238,11 +1269,7 @@ extern "C" int ka_init_k(const ka_graph *g, int m, int64_t K, uint64_t seed, int
       }
       s->own_stream = true;
     }
-    const size_t words = (size_t)s->N * s->W;
-    hipError_t e = hipSuccess;
-    if (e == hipSuccess) e = dalloc(&s->n, words * 8);
-    if (e == hipSuccess) e = dalloc(&s->n0, words * 8);
-    if (e == hipSuccess) e = dalloc(&s->f, words * 8);
+    hipError_t e = alloc_state(s);
     if (e == hipSuccess) e = dalloc(&s->thr_u, (size_t)s->R * 8);
     if (e == hipSuccess) e = dalloc(&s->thr_i, (size_t)s->R * 8);
     if (e == hipSuccess) e = dalloc(&s->err, sizeof(int));

@@ -67,6 +67,7 @@ struct ka_sim {
   // device memory
   ka::u64 *n = nullptr, *n0 = nullptr, *f = nullptr;
   ka::u64 *n_next = nullptr;          // large 2D lattices: second copy of n, swapped with n by each sweep
+  ka::u64 *state_mem[4] = {nullptr, nullptr, nullptr, nullptr};   // allocations behind n, n0, f and n_next
   int32_t *nbr = nullptr;             // graphs: [2(z-1)][E] neighbour lists of the records
   size_t edges_total = 0;             // graphs: E
   int4 *edges = nullptr;
