@@ -648,7 +648,7 @@ def main():
         "dtype": "u64",
         "data": "synthetic",
         "config": {"workload": w["desc"], "sites": N, "replicas": R, "sweeps_per_step": sweeps,
-                   "observations_per_step": len(grid), "path": {1: "global class passes", 2: "LDS-resident"}[path],
+                   "observations_per_step": len(grid), "path": {1: "global class passes", 2: "resident in one workgroup"}[path],
                    "plane_streams": bool(args.plane_streams)},
         "edge_replica_updates_per_s": edges * R * sweeps * args.steps / wall,
         "stream_event_ms": gpu_ms,

@@ -106,10 +106,10 @@ void ka_graph_free(ka_graph *g);
  * that its LDS-resident sweeps generate ahead (at most 8 MiB, allocated on the first such
  * sweep; a layout whose words for a single sweep would exceed 8 MiB draws them in the loop
  * instead), and the state snapshots its ka_run observations are counted from (at most
- * 4 MiB, allocated by the first ka_run that takes them).  For a larger 2D lattice it includes the
- * same words (at most 8 MiB) and, above L = 88, a second copy of n, which its first sweep
- * allocates; a sim that only a batch or a server sweeps takes neither, and the server does not
- * count them. */
+ * 4 MiB, allocated by the first ka_run that takes them).  For a larger 2D lattice, and
+ * 3D L = 20, it includes the same words (at most 8 MiB) and the snapshots or, above L = 88, a
+ * second copy of n, which its first sweep allocates; a sim that only a batch or a server sweeps
+ * takes neither, and the server does not count them. */
 int ka_footprint(const ka_graph *g, int n_replicas, size_t *device_bytes);
 
 /* Create a simulation of n_replicas (a positive multiple of 64) independent replicas on the
@@ -197,11 +197,12 @@ int ka_sim_info(const ka_sim *s, int64_t *N, int *n_replicas, int64_t *K, int *m
  *   KA_OPT_PATH:   0 = automatic, 1 = one kernel per class pass over global memory,
  *                  2 = whole sweep loop inside one workgroup per word plane with the plane in
  *                      LDS (only if it fits; KA_EINVAL otherwise).  Results are identical.
- *                  Paths 0 and 2 run 2D lattices on 4 x 4 blocks of sites held in registers:
- *                  the whole loop in one workgroup per word up to L = 88, above that one to
- *                  three sweeps a launch on tiles of the lattice (class passes while
- *                  KA_OPT_TIMING, KA_OPT_PLANE_STREAMS or KA_OPT_PLANE_GROUPS is set and the word
- *                  plane does not fit in LDS, and under stream capture).
+ *                  Paths 0 and 2 run 2D lattices and 3D L = 16 and 20 on 4 x 4 blocks of
+ *                  sites held in registers: the whole loop in one workgroup per word (2D up
+ *                  to L = 88), larger 2D lattices one to three sweeps a launch on tiles of the
+ *                  lattice (class passes while KA_OPT_TIMING, KA_OPT_PLANE_STREAMS or
+ *                  KA_OPT_PLANE_GROUPS is set and the word plane does not fit in LDS, and
+ *                  under stream capture).
  *   KA_OPT_TIMING: k > 0 brackets every k-th class-pass launch with HIP events on the sim's
  *                  stream (for per-kernel durations, read with ka_timing); 0 = off.
  *   KA_OPT_NOISE:  0 (default) = an independent acceptance bit per replica, edge and sweep;
