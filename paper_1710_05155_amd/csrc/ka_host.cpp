@@ -1010,17 +1010,23 @@ ka::SquareArgs square_args(const ka_sim *s, int64_t t0, int64_t sweeps)
 }
 
 // Resident launch covering sweeps [t_from, t_to) (at most lds_chunk of them) that also takes
-// observations obs[q0..q1) as snapshots (at most lds_snap_rows), which are counted afterwards.
-hipError_t launch_resident(ka_sim *s, int64_t t_from, int64_t t_to, int q0, int q1)
+// observations obs_times[q0..q1) as snapshots (at most lds_snap_rows), which are counted afterwards.
+hipError_t launch_resident(ka_sim *s, int64_t t_from, int64_t t_to, const int64_t *obs_times, int q0, int q1)
 {
   if (t_to == t_from) return observe_rows(s, s->n, s->f, 0, q0, q1 - q0);
   ka::SquareArgs a = square_args(s, t_from, t_to - t_from);
-  a.obs_times = s->obs_d + q0;
   a.n_obs = q1 - q0;
   a.snap = s->lds_snap;
   if (q1 > q0 && (!s->lds_snap || (size_t)(q1 - q0) > s->lds_snap_rows)) return hipErrorInvalidValue;
   const bool flat = s->geom.d == 2;
   hipError_t e = hipSuccess;
+  if (a.n_obs <= ka::kObsArgs) {
+    for (int q = q0; q < q1; ++q) a.obs_at[q - q0] = (uint32_t)(obs_times[q] - t_from);
+  } else {
+    a.obs_times = s->obs_d + q0;
+    e = hipMemcpyAsync(s->obs_d + q0, obs_times + q0, (size_t)a.n_obs * sizeof(int64_t), hipMemcpyHostToDevice, s->stream);
+    if (e != hipSuccess) return e;
+  }
   if (a.acc) e = flat ? ka::launch_square_accept(a, s->stream) : ka::launch_cube_accept(a, s->stream);
   if (e == hipSuccess) e = flat ? ka::launch_square_resident(a, s->m, s->stream) : ka::launch_cube_resident(a, s->m, s->stream);
   if (e == hipSuccess && q1 > q0) {
@@ -1071,7 +1077,7 @@ Route sweep_route(ka_sim *s)
 // them count the state itself.
 hipError_t run_resident(ka_sim *s, const int64_t *obs_times, int n_obs)
 {
-  hipError_t e = hipMemcpyAsync(s->obs_d, obs_times, (size_t)n_obs * sizeof(int64_t), hipMemcpyHostToDevice, s->stream);
+  hipError_t e = hipSuccess;
   const int64_t chunk = lds_chunk(s);
   const size_t fit = kLdsSnapBudget / lds_snap_row_bytes(s->N, s->R);
   const int rows = ensure_lds_snap(s, std::min<size_t>(fit, (size_t)n_obs)) ? (int)std::min<size_t>(fit, (size_t)n_obs) : 0;
@@ -1081,14 +1087,14 @@ hipError_t run_resident(ka_sim *s, const int64_t *obs_times, int n_obs)
     while (q1 < n_obs && obs_times[q1] == a) ++q1;
     const int64_t last = obs_times[n_obs - 1];
     if (q1 > q && (rows == 0 || q1 - q >= rows || last == a)) {
-      e = launch_resident(s, a, a, q, q1);
+      e = launch_resident(s, a, a, obs_times, q, q1);
       q = q1;
       continue;
     }
     int64_t b = std::min(a + chunk, rows > 0 ? last : obs_times[q]);
     while (rows > 0 && q1 < n_obs && obs_times[q1] <= b && q1 - q < rows) ++q1;
     if (rows > 0 && q1 < n_obs && obs_times[q1] <= b) b = obs_times[q1 - 1];   // the buffer is full there
-    e = launch_resident(s, a, b, q, q1);
+    e = launch_resident(s, a, b, obs_times, q, q1);
     q = q1;
     a = b;
   }
@@ -1381,7 +1387,7 @@ extern "C" int ka_sweep(ka_sim *s, int64_t n_sweeps)
       while (done < n_sweeps && e == hipSuccess) {
         const int64_t chunk = std::min(lds_chunk(s), n_sweeps - done);
         if (by == Route::resident) {
-          e = launch_resident(s, s->t + done, s->t + done + chunk, 0, 0);
+          e = launch_resident(s, s->t + done, s->t + done + chunk, nullptr, 0, 0);
         } else {
           e = ensure_obs_buffers(s, 1);
           if (e == hipSuccess) e = launch_lds(s, s->t + done, s->t + done + chunk, 0, 0, false);

@@ -112,7 +112,11 @@ struct SweepLds {
   u64 *snap;
 };
 
-// Lattices on register blocks, one word at a time (ka_square.hip, ka_cube.hip).
+// Lattices on register blocks, one word at a time (ka_square.hip, ka_cube.hip).  The times of up to
+// kObsArgs observations travel with the launch: copying them to the device first is one more
+// dependent operation of a short job (ka_run of one sweep of 2D L = 32: 44.0 us with that copy, 41.3
+// without; of 100 sweeps of L = 64: 412 and 403).
+constexpr int kObsArgs = 16;
 struct SquareArgs {
   u64 *n;
   u64 *f;
@@ -124,9 +128,12 @@ struct SquareArgs {
   u64 *acc;                  // acceptance words drawn ahead (null: drawn in the sweep)
   int n_sweeps;              // sweeps that acc holds, from t0 (resident: all of them run)
   int sweep;                 // tiles: the first of them that this launch runs
-  const int64_t *obs_times;  // resident: observations as snapshots (layout of SweepLds::snap)
+  // resident: observations as snapshots (layout of SweepLds::snap), after obs_at[row] sweeps, or,
+  // with more rows than that holds, at obs_times[row]
+  const int64_t *obs_times;
   int n_obs;
   u64 *snap;
+  uint32_t obs_at[kObsArgs];
 };
 // Positions (4 x 4 blocks) of a lattice that one workgroup holds.
 constexpr int kSquareResidentP = 512;

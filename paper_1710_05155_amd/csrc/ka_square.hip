@@ -297,7 +297,7 @@ __global__ __launch_bounds__(NT) void k_square_resident(SquareArgs a, int m)
   int row = 0;
   const size_t plane_words = (size_t)a.W * (size_t)a.g.N;
   const auto observe = [&](int64_t now) {
-    for (; row < a.n_obs && a.obs_times[row] == now; ++row) {
+    for (; row < a.n_obs && (a.obs_times ? a.obs_times[row] == now : (int64_t)a.t0 + a.obs_at[row] == now); ++row) {
       u64 *dn = a.snap + (size_t)row * 2u * plane_words;
       store(dn, dn + plane_words);
     }
