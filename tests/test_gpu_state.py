@@ -31,3 +31,19 @@ def test_round_trip(kind, size, R):
         bit0 = (arrays[1][b >> 6] >> np.uint64(b & 63)) & np.uint64(1)
         assert dens[b] == int(bit.sum()) and ov[b] == int((bit & bit0).sum())
     s.free()
+
+
+@pytest.mark.parametrize("N,R", [(8, 64), (10920, 64), (10922, 64), (10924, 64), (5460, 128), (5462, 128)])
+def test_small_states_in_one_copy(N, R):
+    """Both sides of 2^15 words in the three arrays, and one array asked for alone."""
+    s = ka.ka_init(ka.ka_graph_rrg(N, 3, 5), 1, 0.5, 2, R)
+    rng = np.random.default_rng(N)
+    arrays = [rng.integers(0, 1 << 63, size=(R // 64, N), dtype=np.uint64) for _ in range(3)]
+    ka.ka_set_state(s, *arrays, 4)
+    got = ka.ka_get_state(s)
+    assert got[3] == 4
+    for x, y in zip(got, arrays):
+        assert np.array_equal(x, y)
+    only = ka.ka_get_state(s, n0=False, f=False)
+    assert only[1] is None and only[2] is None and np.array_equal(only[0], arrays[0])
+    s.free()
