@@ -372,8 +372,11 @@ __global__ __launch_bounds__(4 * P) void k_cube_resident(SquareArgs a, int m)
   observe((int64_t)a.t0);
   const bool odd = az & 1;
   for (int s = 0; s < a.n_sweeps; ++s) {
-    // one class: the work at the places of this wave's z, the words of the class D later, the
-    // barrier, and the words that other threads changed
+    // One class: the work at the places of this wave's z, the words of the class D later, the
+    // barrier, and the words that other threads changed.  Those are read before the next barrier,
+    // so the next class must not write them from another thread.  One pair of classes does: after
+    // (1, 3) the blocks at z mod 4 = 3 take sites (1, 0) and (3, 0), which class (2, 0) writes from
+    // the plane below; a barrier of its own orders the two.
 #define KA_CUBE_XY(MU, R)                                                                          \
     if (odd) t.template work_xy<MU, (R ^ 2), GIVEN>(r[(4 * MU + R) % D], g, 4 * MU + R, m);        \
     else t.template work_xy<MU, R, GIVEN>(r[(4 * MU + R) % D], g, 4 * MU + R, m);                  \
@@ -396,6 +399,7 @@ __global__ __launch_bounds__(4 * P) void k_cube_resident(SquareArgs a, int m)
     KA_CUBE_XY(1, 1)
     KA_CUBE_XY(1, 2)
     KA_CUBE_XY(1, 3)
+    __syncthreads();
     KA_CUBE_Z(0)
     KA_CUBE_Z(1)
     KA_CUBE_Z(2)
