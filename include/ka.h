@@ -201,8 +201,10 @@ int ka_sim_info(const ka_sim *s, int64_t *N, int *n_replicas, int64_t *K, int *m
  *                  sites held in registers: the whole loop in one workgroup per word (2D up
  *                  to L = 88), larger 2D lattices one to three sweeps a launch on tiles of the
  *                  lattice (class passes while KA_OPT_TIMING, KA_OPT_PLANE_STREAMS or
- *                  KA_OPT_PLANE_GROUPS is set and the word plane does not fit in LDS, and
- *                  under stream capture).
+ *                  KA_OPT_PLANE_GROUPS is set and the word plane does not fit in LDS, under
+ *                  stream capture, and for the rest of a sim's life once a ka_sweep of it has
+ *                  been captured: tiles move the state between two copies, and a captured sweep
+ *                  keeps the address of one).
  *   KA_OPT_TIMING: k > 0 brackets every k-th class-pass launch with HIP events on the sim's
  *                  stream (for per-kernel durations, read with ka_timing); 0 = off.
  *   KA_OPT_NOISE:  0 (default) = an independent acceptance bit per replica, edge and sweep;

@@ -607,9 +607,10 @@ Route route(const ka_sim *s)
   // fits in LDS).
   if (!use_lds(s) && (s->plane_streams || s->plane_group_opt >= 0 || s->timing_every > 0)) return Route::passes;
   if (s->geom.d == 3 && s->geom.P < ka::kCubeMinP) return Route::lds;
-  // A capture cannot allocate, nor can its replays swap the two copies of n.
+  // A capture cannot allocate, nor can its replays swap the two copies of n; and once a graph holds
+  // n's address, n stays there.
   if (capturing(s) && !(small && use_lds(s))) return Route::passes;
-  return small ? Route::resident : Route::tiles;
+  return small ? Route::resident : s->captured ? Route::passes : Route::tiles;
 }
 
 hipEvent_t pooled_event(ka_sim *s)
@@ -1381,6 +1382,7 @@ extern "C" int ka_sweep(ka_sim *s, int64_t n_sweeps)
     if (s->t + n_sweeps >= (1ll << 32)) return fail(KA_ESTATE, "sweep index would reach 2^32");
     DeviceGuard dg(s->device);
     hipError_t e = hipSuccess;
+    if (capturing(s)) s->captured = true;
     const Route by = sweep_route(s);
     if (by == Route::resident || by == Route::lds) {
       int64_t done = 0;

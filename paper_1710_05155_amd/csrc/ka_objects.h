@@ -85,6 +85,7 @@ struct ka_sim {
   struct ka_batch *batch = nullptr;
   // options and timing
   bool init_checked = false;
+  bool captured = false;          // a graph of the caller's holds a sweep of this sim, and with it n's address
   int path_opt = 0;
   int noise = 0;                  // KA_OPT_NOISE
   int plane_streams = 0;          // KA_OPT_PLANE_STREAMS
