@@ -857,11 +857,11 @@ int max_class_edges(const std::vector<int> &class_start)
 }
 
 // Sweeps per LDS-resident launch of this sim; when its layout takes pre-generated acceptance
-// words, allocates their buffer on first use (if that fails, the words are drawn in the loop
-// and launches cover up to kLdsChunk sweeps).
+// words, allocates their buffer on first use (if that fails, and in a capture, which cannot
+// allocate, the words are drawn in the loop and launches cover up to kLdsChunk sweeps).
 int64_t lds_chunk(ka_sim *s)
 {
-  if (!s->lds_acc_tried) {
+  if (!s->lds_acc_tried && !capturing(s)) {
     s->lds_acc_tried = true;
     size_t bytes = 0;
     const int64_t sweeps = s->lattice ? block_acc_plan(s->geom.d, s->geom.P, s->W, &bytes)
@@ -1380,6 +1380,7 @@ extern "C" int ka_sweep(ka_sim *s, int64_t n_sweeps)
     if (rc) return rc;
     if (n_sweeps < 0) return fail(KA_EINVAL, "n_sweeps < 0");
     if (s->t + n_sweeps >= (1ll << 32)) return fail(KA_ESTATE, "sweep index would reach 2^32");
+    if (n_sweeps == 0) return KA_OK;
     DeviceGuard dg(s->device);
     hipError_t e = hipSuccess;
     if (capturing(s)) s->captured = true;
@@ -1424,8 +1425,12 @@ extern "C" int ka_run(ka_sim *s, const int64_t *obs_times, int n_obs, int64_t *d
     if (e != hipSuccess) return fail(KA_ENOMEM, "observation buffers: %s", hipGetErrorString(e));
     const size_t cbytes = (size_t)n_obs * 3u * (size_t)s->R * sizeof(unsigned long long);
     e = hipMemsetAsync(s->counts, 0, cbytes, s->stream);
-    const Route by = sweep_route(s);
-    if (e == hipSuccess && by == Route::resident) {
+    const bool sweeps = prev > s->t;
+    const Route by = sweeps ? sweep_route(s) : Route::passes;
+    if (e == hipSuccess && !sweeps) {
+      // counts of the state as it is: none of the buffers that sweeps take
+      e = observe_rows(s, s->n, s->f, 0, 0, n_obs);
+    } else if (e == hipSuccess && by == Route::resident) {
       e = run_resident(s, obs_times, n_obs);
     } else if (e == hipSuccess && by == Route::lds) {
       e = hipMemcpyAsync(s->obs_d, obs_times, (size_t)n_obs * sizeof(int64_t), hipMemcpyHostToDevice, s->stream);
