@@ -102,14 +102,15 @@ void ka_graph_free(ka_graph *g);
 
 /* Device bytes a sim of this graph with n_replicas replicas allocates (serving admission).
  * No passage of the paper applies: this is library bookkeeping.
- * For an instance whose word plane fits in LDS this includes the buffer of acceptance words
- * that its LDS-resident sweeps generate ahead (at most 8 MiB, allocated on the first such
- * sweep; a layout whose words for a single sweep would exceed 8 MiB draws them in the loop
- * instead), and the state snapshots its ka_run observations are counted from (at most
- * 4 MiB, allocated by the first ka_run that takes them).  For a larger 2D lattice, and
- * 3D L = 20, it includes the same words (at most 8 MiB) and the snapshots or, above L = 88, a
- * second copy of n, which its first sweep allocates; a sim that only a batch or a server sweeps
- * takes neither, and the server does not count them. */
+ * Besides the state, the schedule and one row of counts it includes what the sim's own sweeps
+ * allocate on first use: the acceptance words drawn ahead (at most 8 MiB; none on instances that
+ * run as class passes, or where the words of a single sweep would exceed 8 MiB), and the state
+ * snapshots that ka_run observations are counted from (at most 4 MiB) or, for 2D lattices above
+ * L = 88, a second copy of n; and the observation buffer as ka_get_state, ka_set_state and
+ * ka_observe_pairs may leave it (at most about 256 KiB).  Not included: count rows of ka_run
+ * beyond that, and the staging that a state copy of a larger sim holds while it runs (at most
+ * 32 MiB).  A sim that only a batch or a server sweeps takes no second copy of n, and the server
+ * does not count one: it admits a job by at most this figure. */
 int ka_footprint(const ka_graph *g, int n_replicas, size_t *device_bytes);
 
 /* Create a simulation of n_replicas (a positive multiple of 64) independent replicas on the
@@ -336,7 +337,7 @@ void ka_batch_free(ka_batch *b);
 /* ------------------------------------------------------------------------------------ */
 /* Serving: a job server with continuous batching.  A worker thread owns one stream and  */
 /* one batch; submitted jobs wait in FIFO order until a slot is free and their device    */
-/* footprint (ka_footprint) fits the budget, then are initialised on the device and join */
+/* footprint (at most ka_footprint) fits the budget, then are initialised on the device and join */
 /* the batch, so jobs that arrive while others run share the same step kernels.  A job's */
 /* observation times cut it into batch segments; at each one the per-replica counts of   */
 /* ka_observe are taken on the device and copied back without stopping the batch.  Each  */

@@ -878,6 +878,10 @@ int64_t lds_chunk(ka_sim *s)
   return s->lds_acc ? s->lds_acc_sweeps : kLdsChunk;
 }
 
+// Staging of state copies: kept with the sim up to 2^15 words (256 KiB, in the observation buffer),
+// otherwise allocated for the call, 2^22 words (32 MiB) at most.
+constexpr int64_t kStateKept = 1 << 15, kStateStaging = 1 << 22;
+
 hipError_t ensure_obs_buffers(ka_sim *s, size_t n_obs)
 {
   const size_t need = n_obs * 3u * (size_t)s->R;
@@ -1169,35 +1173,83 @@ int check_sim(const ka_sim *s)
 
 }  // namespace
 
-// Device bytes of a sim that only a batch sweeps (it takes no buffers of its own for sweeps of a
-// large 2D lattice).
+namespace {
+
+// State, schedule, selection thresholds, one row of counts and the full-element summary.
+size_t base_bytes(const ka_graph *g, int n_replicas)
+{
+  return state_bytes(g->N, n_replicas) + graph_device_bytes(g) + (size_t)n_replicas * 16u +
+         (size_t)3 * n_replicas * 8u + 64u + (g->lattice ? 0 : fsat_bytes(g->N, n_replicas));
+}
+
+// Whether a word plane fits in LDS.
+bool plane_fits_lds(const ka_graph *g, int n_replicas)
+{
+  const int wpt = ((n_replicas / 64) % 2 == 0) ? 2 : 1;
+  return ka::sweep_lds_bytes((int)g->N, wpt) + 4096 <= (size_t)ka::max_lds_bytes();
+}
+
+size_t snapshot_bytes(const ka_graph *g, int n_replicas)
+{
+  const size_t row = lds_snap_row_bytes(g->N, n_replicas);
+  return (kLdsSnapBudget / row) * row;
+}
+
+// Words drawn ahead of the LDS sweeps of a general graph.
+size_t graph_draw_bytes(const ka_graph *g, int n_replicas)
+{
+  std::vector<int> cs((size_t)g->C + 1, 0);
+  for (int32_t c : g->ecls) cs[(size_t)c + 1] += 1;
+  for (size_t c = 1; c < cs.size(); ++c) cs[c] += cs[c - 1];
+  size_t acc = 0;
+  (void)lds_acc_plan_graph((int64_t)g->ecls.size(), max_class_edges(cs), g->z, n_replicas, &acc);
+  return acc;
+}
+
+// What a sim's own sweeps allocate on first use: words drawn ahead, and snapshots or a second copy of n.
+size_t sweep_bytes(const ka_graph *g, int n_replicas)
+{
+  if (!g->lattice) return plane_fits_lds(g, n_replicas) ? graph_draw_bytes(g, n_replicas) + snapshot_bytes(g, n_replicas) : 0;
+  const int64_t P = g->N / (g->d == 2 ? 16 : 64);
+  const bool small = block_resident(g->d, P);
+  if (g->d == 3 && !small) return 0;
+  size_t draws = 0;
+  (void)block_acc_plan(g->d, P, n_replicas / 64, &draws);
+  return draws + (small ? snapshot_bytes(g, n_replicas) : (size_t)g->N * (size_t)(n_replicas / 64) * 8u);
+}
+
+// What state copies and pair sums leave in the observation buffer beyond its first row.
+size_t kept_bytes(const ka_graph *g, int n_replicas)
+{
+  const size_t row = 3u * (size_t)n_replicas;
+  const size_t words = std::max<size_t>((size_t)std::min<int64_t>(3 * g->N * (n_replicas / 64), kStateKept),
+                                        g->lattice ? 2u * ka::kMaxPairShells : 0u);
+  return ((words + row - 1) / row) * (row + 1u) * 8u;
+}
+
+}  // namespace
+
+// What the job server admits by, for a sim that only a batch sweeps.  An instance whose word plane
+// fits in LDS counts with room for draws and snapshots, which a batch does not take, so that a budget
+// holds no more of them at once than it ever did: on lattices, one class's words on each of 1024
+// threads' edge slots, for up to 8 MiB of sweeps.
 int ka_sim_batch_bytes(const ka_graph *g, int n_replicas, size_t *device_bytes)
 {
   if (!g || !device_bytes) return fail(KA_EINVAL, "NULL argument");
   if (n_replicas <= 0 || n_replicas % 64 != 0) return fail(KA_EINVAL, "n_replicas must be a positive multiple of 64");
-  *device_bytes = state_bytes(g->N, n_replicas) + graph_device_bytes(g) +
-                  (size_t)n_replicas * 16u + (size_t)3 * n_replicas * 8u + 64u +
-                  (g->lattice ? 0 : fsat_bytes(g->N, n_replicas));
-  const int wpt = ((n_replicas / 64) % 2 == 0) ? 2 : 1;
-  if (ka::sweep_lds_bytes((int)g->N, wpt) + 4096 <= (size_t)ka::max_lds_bytes()) {
-    // an instance on the LDS-resident path adds its pre-generated acceptance words and its
-    // observation snapshots
-    size_t acc = 0;
-    if (g->lattice) {
-      // room for one class's words on each of 1024 threads' edge slots, for up to 8 MiB of sweeps
-      const int64_t P = g->N / (g->d == 2 ? 16 : 64);
-      const size_t slots = (size_t)(((g->d == 2 ? 4 : 16) * P + 1023) / 1024);
-      const size_t per_sweep = (size_t)(n_replicas / 64) * (size_t)(4 * g->d) * slots * 1024u * 8u;
-      if (per_sweep <= kLdsAccBudget && !(g->d == 3 && wpt == 2 && slots > 1)) acc = std::min<size_t>(kLdsChunk, kLdsAccBudget / per_sweep) * per_sweep;
-    } else {
-      std::vector<int> cs((size_t)g->C + 1, 0);
-      for (int32_t c : g->ecls) cs[(size_t)c + 1] += 1;
-      for (size_t c = 1; c < cs.size(); ++c) cs[c] += cs[c - 1];
-      (void)lds_acc_plan_graph((int64_t)g->ecls.size(), max_class_edges(cs), g->z, n_replicas, &acc);
-    }
-    const size_t row = lds_snap_row_bytes(g->N, n_replicas);
-    *device_bytes += acc + (kLdsSnapBudget / row) * row;
+  *device_bytes = base_bytes(g, n_replicas);
+  if (!plane_fits_lds(g, n_replicas)) return KA_OK;
+  if (!g->lattice) {
+    *device_bytes += graph_draw_bytes(g, n_replicas);
+  } else {
+    const int64_t P = g->N / (g->d == 2 ? 16 : 64);
+    const int W = n_replicas / 64;
+    const size_t slots = (size_t)(((g->d == 2 ? 4 : 16) * P + 1023) / 1024);
+    const size_t per_sweep = (size_t)W * (size_t)(4 * g->d) * slots * 1024u * 8u;
+    if (per_sweep <= kLdsAccBudget && !(g->d == 3 && W % 2 == 0 && slots > 1))
+      *device_bytes += std::min<size_t>(kLdsChunk, kLdsAccBudget / per_sweep) * per_sweep;
   }
+  *device_bytes += snapshot_bytes(g, n_replicas);
   return KA_OK;
 }
 
@@ -1205,19 +1257,9 @@ extern "C" int ka_footprint(const ka_graph *g, int n_replicas, size_t *device_by
 {
   return ka_guard([&]() -> int {
     const int rc = ka_sim_batch_bytes(g, n_replicas, device_bytes);
-    if (rc != KA_OK || !g->lattice) return rc;
-    // what the sim's own sweeps on register blocks take beyond that: words drawn ahead, and
-    // snapshots or a second copy of n
-    const int64_t P = g->N / (g->d == 2 ? 16 : 64);
-    const bool small = block_resident(g->d, P);
-    if (g->d == 3 && !small) return KA_OK;
-    const int wpt = ((n_replicas / 64) % 2 == 0) ? 2 : 1;
-    const bool fits = ka::sweep_lds_bytes((int)g->N, wpt) + 4096 <= (size_t)ka::max_lds_bytes();
-    const size_t row = lds_snap_row_bytes(g->N, n_replicas);
-    size_t draws = 0;
-    (void)block_acc_plan(g->d, P, n_replicas / 64, &draws);   // those of a sim whose word plane fits in LDS are counted there
-    if (!fits) *device_bytes += draws + (small ? (kLdsSnapBudget / row) * row : 0);
-    if (!small) *device_bytes += (size_t)g->N * (size_t)(n_replicas / 64) * 8u;
+    if (rc != KA_OK) return rc;
+    const size_t own = base_bytes(g, n_replicas) + sweep_bytes(g, n_replicas) + kept_bytes(g, n_replicas);
+    *device_bytes = std::max(*device_bytes, own);   // a budget of this size also holds the sim as a server's job
     return KA_OK;
   });
 }
@@ -1738,10 +1780,6 @@ extern "C" int ka_observe_pairs(ka_sim *s, int r2_max, int64_t *S2, int64_t *S11
 }
 
 namespace {
-
-// Staging of state copies: kept with the sim up to 2^15 words (256 KiB, in the observation buffer),
-// otherwise allocated for the call, 2^22 words (32 MiB) at most.
-constexpr int64_t kStateKept = 1 << 15, kStateStaging = 1 << 22;
 
 struct StateStaging {
   u64 *words = nullptr;

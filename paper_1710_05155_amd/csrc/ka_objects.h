@@ -121,8 +121,8 @@ int ka_sim_steps_per_sweep(const ka_sim *s);
 // planes in the sim's groups as ka_sweep runs them (each group through all `count` launches
 // before the next); s->t is left as it is.  A batch runs its one-at-a-time members with it.
 hipError_t ka_sim_passes(ka_sim *s, int64_t p0, int64_t count, hipStream_t stream);
-// Device bytes of a sim that only a batch sweeps: ka_footprint without the buffers that its own
-// sweeps of a large 2D lattice take.
+// Device bytes that the job server admits a sim by: at most ka_footprint, without the buffers that its
+// own sweeps of a large 2D lattice take.
 int ka_sim_batch_bytes(const ka_graph *g, int n_replicas, size_t *device_bytes);
 // Counts of ka_observe enqueued on the sim's stream into pinned host memory (3 * R values).
 int ka_sim_observe_async(ka_sim *s, unsigned long long *host_out);
