@@ -13,12 +13,12 @@
 #include <mutex>
 #include <new>
 #include <string>
-#include <thread>
 #include <utility>
 #include <vector>
 
 #include "ka_internal.h"
 #include "ka_objects.h"
+#include "ka_touch.h"
 
 using ka::u64;
 
@@ -1868,39 +1868,6 @@ hipError_t move_small_state(ka_sim *s, const StateStaging &st, uint64_t *const h
       if (host[k]) std::copy(all.begin() + (ptrdiff_t)(k * words), all.begin() + (ptrdiff_t)((k + 1) * words), host[k]);
   return e;
 }
-
-// Touches the pages of arrays that are about to be written whole, so that a large export is
-// not bound by their first use on one thread (fresh memory is copied to at 4 GB/s, touched memory
-// at 17).  Ends with the object.
-class PageToucher {
- public:
-  void add(uint64_t *p, size_t bytes)
-  {
-    constexpr size_t kWorth = (size_t)4 << 20;
-    constexpr int kThreads = 4;
-    if (!p || bytes < kWorth) return;
-    char *base = reinterpret_cast<char *>(p);
-    for (int k = 0; k < kThreads; ++k) {
-      const size_t a = bytes / kThreads * k, b = k + 1 < kThreads ? bytes / kThreads * (k + 1) : bytes;
-      try {
-        threads_.emplace_back([base, a, b] {
-          for (size_t q = a; q < b; q += 4096) *reinterpret_cast<volatile char *>(base + q) = 0;
-        });
-      } catch (...) {
-        return;   // no more threads: the copy touches the rest itself
-      }
-    }
-  }
-  void wait()
-  {
-    for (std::thread &t : threads_) t.join();
-    threads_.clear();
-  }
-  ~PageToucher() { wait(); }
-
- private:
-  std::vector<std::thread> threads_;
-};
 
 }  // namespace
 
