@@ -192,11 +192,11 @@ __device__ void select_full(const InitArgs &a, int b, Select &s)
   rank_candidates(s, need);
 }
 
-// Small instances: the threshold of replica blockIdx.x.
+// Small instances: the threshold of replica a.first + blockIdx.x.
 __global__ __launch_bounds__(kSelBlock) void k_init_select(InitArgs a)
 {
   __shared__ Select s;
-  const int b = (int)blockIdx.x;
+  const int b = a.first + (int)blockIdx.x;
   if (a.K > 0) select_full(a, b, s);
   if (threadIdx.x == 0) {
     a.thr_u[b] = a.K > 0 ? s.thr_u : 0;
@@ -213,7 +213,7 @@ template <int WPT>
 __global__ __launch_bounds__(kFillBlock) void k_init_fill(InitArgs a)
 {
   __shared__ u64 bits[64];
-  const int word = (int)blockIdx.y;
+  const int word = a.first + (int)blockIdx.y;
   const int lane = (int)__lane_id();
   const int q = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int idx = (int)blockIdx.x * 64 + lane;
@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kKeysBlock) void k_init_keys(InitArgs a)
   __shared__ unsigned cnt[RB], first[RB], below[RB];
   __shared__ uint2 ent[kKeysEntries];   // element, replica of the plane | slot << 8
   __shared__ unsigned total;
-  const int plane = (int)blockIdx.y;
+  const int plane = a.first + (int)blockIdx.y;
   const int tid = (int)threadIdx.x;
   const int lane = (int)__lane_id();
   for (int q = tid; q < RB; q += kKeysBlock) cnt[q] = below[q] = 0;
@@ -348,12 +348,12 @@ __global__ __launch_bounds__(kKeysBlock) void k_init_keys(InitArgs a)
   }
 }
 
-// The threshold of replica blockIdx.x among its candidates, and the bits of those at or below it.
+// The threshold of replica a.first + blockIdx.x among its candidates, and the bits of those at or below it.
 template <int WPT>
 __global__ __launch_bounds__(kSelBlock) void k_init_pick(InitArgs a)
 {
   __shared__ Select s;
-  const int b = (int)blockIdx.x;
+  const int b = a.first + (int)blockIdx.x;
   const int tid = (int)threadIdx.x;
   const int word = b >> 6;
   u64 *n = a.n + (size_t)(word / WPT) * (size_t)a.N * WPT + (size_t)(word % WPT);   // + idx * WPT
@@ -427,19 +427,30 @@ __global__ void k_init_clear(unsigned *counters, int n, int *err)
 // Smallest N of the window selection: its lists (N/16 sites per replica) hold the widest window.
 constexpr int kWindowMinN = 1 << 14;
 
+// A grid holds fewer than 2^32 threads in x and 2^16 workgroups in y, and a launch beyond that runs
+// with the number of them cut off, without an error; so larger ones are made in parts.
+template <typename Launch>
+void in_parts(InitArgs a, int total, int part, Launch launch)
+{
+  for (a.first = 0; a.first < total; a.first += part) launch(a, (unsigned)std::min(part, total - a.first));
+}
+constexpr int kGridX = 1 << 21, kGridY = 1 << 15;   // at most 1024 threads a workgroup
+
 }  // namespace
 
 hipError_t launch_init(const InitArgs &args, int R, int wpt, hipStream_t s)
 {
   InitArgs a = args;
   const int words = R / 64;
-  hipLaunchKernelGGL(k_init_clear, dim3((unsigned)((2 * R + 255) / 256)), dim3(256), 0, s, reinterpret_cast<unsigned *>(a.thr_u),
+  hipLaunchKernelGGL(k_init_clear, dim3((unsigned)((2 * (size_t)R + 255) / 256)), dim3(256), 0, s, reinterpret_cast<unsigned *>(a.thr_u),
                      2 * R, a.err);
   if (a.N < kWindowMinN) {
-    hipLaunchKernelGGL(k_init_select, dim3((unsigned)R), dim3(kSelBlock), 0, s, a);
-    const dim3 grid((unsigned)((a.N + 63) / 64), (unsigned)words);
-    if (wpt == 2) hipLaunchKernelGGL((k_init_fill<2>), grid, dim3(kFillBlock), 0, s, a);
-    else hipLaunchKernelGGL((k_init_fill<1>), grid, dim3(kFillBlock), 0, s, a);
+    in_parts(a, R, kGridX, [&](const InitArgs &p, unsigned n) { hipLaunchKernelGGL(k_init_select, dim3(n), dim3(kSelBlock), 0, s, p); });
+    in_parts(a, words, kGridY, [&](const InitArgs &p, unsigned n) {
+      const dim3 grid((unsigned)((a.N + 63) / 64), n);
+      if (wpt == 2) hipLaunchKernelGGL((k_init_fill<2>), grid, dim3(kFillBlock), 0, s, p);
+      else hipLaunchKernelGGL((k_init_fill<1>), grid, dim3(kFillBlock), 0, s, p);
+    });
     return hipGetLastError();
   }
   // Window of 4.5 standard deviations of the K-th key and 12 sites to either side (the second
@@ -455,14 +466,14 @@ hipError_t launch_init(const InitArgs &args, int R, int wpt, hipStream_t s)
   a.cap = a.N >> 4;
   // 2048 workgroups fill the device (8 waves a SIMD)
   const unsigned bx = (unsigned)std::min((a.N + kKeysBlock - 1) / kKeysBlock, std::max(1, 2048 / a.planes));
-  const dim3 grid(bx, (unsigned)a.planes);
-  if (wpt == 2) {
-    hipLaunchKernelGGL((k_init_keys<2>), grid, dim3(kKeysBlock), 0, s, a);
-    hipLaunchKernelGGL((k_init_pick<2>), dim3((unsigned)R), dim3(kSelBlock), 0, s, a);
-  } else {
-    hipLaunchKernelGGL((k_init_keys<1>), grid, dim3(kKeysBlock), 0, s, a);
-    hipLaunchKernelGGL((k_init_pick<1>), dim3((unsigned)R), dim3(kSelBlock), 0, s, a);
-  }
+  in_parts(a, a.planes, kGridY, [&](const InitArgs &p, unsigned n) {
+    if (wpt == 2) hipLaunchKernelGGL((k_init_keys<2>), dim3(bx, n), dim3(kKeysBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_init_keys<1>), dim3(bx, n), dim3(kKeysBlock), 0, s, p);
+  });
+  in_parts(a, R, kGridX, [&](const InitArgs &p, unsigned n) {
+    if (wpt == 2) hipLaunchKernelGGL((k_init_pick<2>), dim3(n), dim3(kSelBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_init_pick<1>), dim3(n), dim3(kSelBlock), 0, s, p);
+  });
   const size_t total = (size_t)a.N * (size_t)words;
   hipLaunchKernelGGL(k_init_copy, dim3((unsigned)std::min<size_t>((total + 255) / 256, 4096)), dim3(256), 0, s, a.n, a.n0, a.f, total);
   return hipGetLastError();

@@ -167,6 +167,7 @@ struct InitArgs {
   uint32_t lo, width;
   u64 bin_mul;
   int cap;
+  int first;   // first replica, word or plane of this launch
 };
 
 struct ObserveArgs {

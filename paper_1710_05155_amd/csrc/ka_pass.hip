@@ -255,11 +255,20 @@ hipError_t launch_observe(const ObserveArgs &a, int wpt, hipStream_t s)
   const int sets = (int)std::min<int64_t>((int64_t)a.planes * a.rows, kObsBlocks);   // planes x states
   const int spread = std::max((chunks + 3) / 4, std::min(chunks, kObsSpread / sets));
   const int bx = std::max(1, std::min(spread, std::min(kObsPlaneBlocks, kObsBlocks / sets)));
-  const dim3 grid((unsigned)bx, (unsigned)a.planes, (unsigned)a.rows);
-  if (wpt == 2)
-    hipLaunchKernelGGL((k_observe<2>), grid, dim3(kObsBlock), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_observe<1>), grid, dim3(kObsBlock), 0, s, a);
+  // a grid holds fewer than 2^16 workgroups in y: more planes than that are counted in parts
+  constexpr int kGridY = 1 << 15;
+  for (int first = 0; first < a.planes; first += kGridY) {
+    ObserveArgs p = a;
+    const size_t words = (size_t)first * (size_t)wpt;
+    p.n += words * (size_t)a.N;
+    p.n0 += words * (size_t)a.N;
+    p.f += words * (size_t)a.N;
+    p.out += words * 64u;
+    p.planes = std::min(kGridY, a.planes - first);
+    const dim3 grid((unsigned)bx, (unsigned)p.planes, (unsigned)a.rows);
+    if (wpt == 2) hipLaunchKernelGGL((k_observe<2>), grid, dim3(kObsBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_observe<1>), grid, dim3(kObsBlock), 0, s, p);
+  }
   return hipGetLastError();
 }
 
