@@ -1710,9 +1710,7 @@ extern "C" int ka_observe_pairs(ka_sim *s, int r2_max, int64_t *S2, int64_t *S11
     // larger (dz, dy, dx) is computed.
     int halo = 0;
     while (halo < L / 2 && (halo + 1) * (halo + 1) <= r2_max) ++halo;
-    int rows = 0, words = 0;
-    const bool tiles = ka::pairs_tile_rows(L, halo, r2_max, &rows, &words);
-    std::vector<int4> disp;
+    std::vector<int4> disp;   // (dx, dy, dz, 2 * r2 + 1 if it counts twice)
     std::vector<int64_t> cnt((size_t)r2_max + 1, 0);
     std::vector<int> start;
     const int hz = d == 3 ? halo : 0;
@@ -1727,27 +1725,33 @@ extern "C" int ka_observe_pairs(ka_sim *s, int r2_max, int64_t *S2, int64_t *S11
           const int oz = opposite(dz), oy = opposite(dy), ox = opposite(dx);
           const auto one = std::make_pair(dz, std::make_pair(dy, dx)), other = std::make_pair(oz, std::make_pair(oy, ox));
           if (one < other) continue;
-          const int times = one == other ? 1 : 2;
-          disp.push_back(tiles ? make_int4(dy * (L + 2 * halo) + dx, r2, times, 0) : make_int4(dx, dy, dz, 2 * r2 + times - 1));
+          disp.push_back(make_int4(dx, dy, dz, 2 * r2 + (one == other ? 0 : 1)));
         }
     }
     start.push_back((int)disp.size());
-    if (tiles)
+    const int n_disp = start.back();
+    const ka::PairTiles tiles = ka::pairs_tiles(s->geom, s->W, halo, n_disp, r2_max);
+    if (tiles.rows > 0) {
+      for (int4 &v : disp) v = make_int4(v.y * (L + 2 * halo) + v.x, v.w >> 1, 1 + (v.w & 1), 0);
       for (size_t k = 0; k + 1 < start.size(); ++k) {
         const auto key = [](const int4 &v) { return std::make_pair(v.y, v.z); };
         std::sort(disp.begin() + start[k], disp.begin() + start[k + 1], [&](const int4 &u, const int4 &v) { return key(u) < key(v); });
         for (int q = start[k]; q < start[k + 1]; ++q) disp[(size_t)q].w = q + 1 == start[k + 1] || key(disp[(size_t)q]) != key(disp[(size_t)q + 1]);
       }
+    }
+    // the starts follow the displacements, in the same copy
+    for (size_t k = 0; k < start.size(); k += 4) {
+      const auto at = [&](size_t q) { return q < start.size() ? start[q] : 0; };
+      disp.push_back(make_int4(at(k), at(k + 1), at(k + 2), at(k + 3)));
+    }
     DeviceGuard dg(s->device);
-    int4 *d_disp = nullptr;   // displacements, then the starts
+    int4 *d_disp = nullptr;
     const size_t shells = (size_t)r2_max + 1;
     const size_t disp_bytes = disp.size() * sizeof(int4);
     hipError_t e = ensure_obs_buffers(s, (2 * shells + 3u * (size_t)s->R - 1) / (3u * (size_t)s->R));
     unsigned long long *d_out = s->counts;
-    if (e == hipSuccess) e = dalloc(&d_disp, disp_bytes + start.size() * sizeof(int));
-    int *d_start = reinterpret_cast<int *>(d_disp + disp.size());
+    if (e == hipSuccess) e = dalloc(&d_disp, disp_bytes);
     if (e == hipSuccess) e = hipMemcpyAsync(d_disp, disp.data(), disp_bytes, hipMemcpyHostToDevice, s->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d_start, start.data(), start.size() * sizeof(int), hipMemcpyHostToDevice, s->stream);
     if (e == hipSuccess) e = hipMemsetAsync(d_out, 0, 2 * shells * sizeof(unsigned long long), s->stream);
     if (e == hipSuccess) {
       ka::PairArgs a{};
@@ -1756,14 +1760,14 @@ extern "C" int ka_observe_pairs(ka_sim *s, int r2_max, int64_t *S2, int64_t *S11
       a.g = s->geom;
       a.planes = s->planes;
       a.disp = d_disp;
-      a.n_disp = (int)disp.size();
-      a.start = d_start;
+      a.n_disp = n_disp;
+      a.start = reinterpret_cast<const int *>(d_disp + n_disp);
       a.halo = halo;
-      a.rows = rows;
+      a.tiles = tiles;
       a.r2_max = r2_max;
       a.S2 = d_out;
       a.S11 = d_out + shells;
-      e = tiles ? ka::launch_pairs_tile(a, s->wpt, words, s->stream) : ka::launch_pairs(a, s->wpt, s->stream);
+      e = tiles.rows > 0 ? ka::launch_pairs_tile(a, s->wpt, s->stream) : ka::launch_pairs(a, s->wpt, s->stream);
     }
     std::vector<unsigned long long> host(2 * shells);
     if (e == hipSuccess) e = hipMemcpyAsync(host.data(), d_out, 2 * shells * sizeof(unsigned long long), hipMemcpyDeviceToHost, s->stream);

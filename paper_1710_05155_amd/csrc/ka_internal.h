@@ -223,6 +223,11 @@ hipError_t launch_state(const StateArgs &a, bool out, hipStream_t s);
 
 // Spatial four-point sums (ka_pairs.hip).
 constexpr int kMaxPairShells = 2049;   // r2_max <= 2048
+// How the tile kernel splits a sum: rows of a workgroup (0: the gather kernel runs), words at a
+// time, and parts of each list of displacements, which are different workgroups.
+struct PairTiles {
+  int rows, words, parts;
+};
 struct PairArgs {
   const u64 *n;
   const u64 *n0;
@@ -235,15 +240,15 @@ struct PairArgs {
   int n_disp;
   const int *start;
   int halo;                            // tiles: largest component, at most L / 2
-  int rows;                            // tiles: rows of a workgroup
+  PairTiles tiles;
   int r2_max;
   unsigned long long *S2;              // [r2_max + 1]
   unsigned long long *S11;
 };
 hipError_t launch_pairs(const PairArgs &a, int wpt, hipStream_t s);
-// Rows and words at a time of the tile kernel; false if the halo's tile does not fit in LDS.
-bool pairs_tile_rows(int L, int halo, int r2_max, int *rows, int *words);
-hipError_t launch_pairs_tile(const PairArgs &a, int wpt, int words, hipStream_t s);
+// The faster kernel for W words and n_disp displacements, and its split.
+PairTiles pairs_tiles(const LatticeGeom &g, int W, int halo, int n_disp, int r2_max);
+hipError_t launch_pairs_tile(const PairArgs &a, int wpt, hipStream_t s);
 // Graphs without a geometry: out[0] += sum_i Q_i, out[1] += sum_i Q_i^2 with Q_i the number
 // of replicas b with n_i^b(t) n_i^b(0) = 1.
 struct PairGraphArgs {

@@ -12,7 +12,8 @@
 // k_pairs_tile: a workgroup takes some rows of one plane, with the Q words and replica sums of the
 // plane dz above (their halo included) in LDS; for every displacement with that dz a thread ANDs
 // its sites' Q, held in registers, with the words at one offset from them.  k_pairs, one thread
-// per site gathering from global memory, covers radii whose halo does not fit in LDS.
+// per site gathering from global memory, covers radii whose halo does not fit in LDS, and those
+// where loading the tiles would take longer than the gathers (pairs_tiles).
 #include <algorithm>
 
 #include "ka_device.h"
@@ -23,7 +24,7 @@ namespace {
 using namespace dev;
 
 constexpr int kPairBlock = 256;
-constexpr int kPairChunk = 32;     // displacements per workgroup
+constexpr int kPairChunk = 32;     // most displacements of a workgroup
 constexpr int kMaxWords = 16;      // up to 1024 replicas
 constexpr int kTileBlock = 512, kTileSites = 2;   // threads of k_pairs_tile, sites per thread
 constexpr size_t kTileLds = 80 << 10;   // two workgroups to a CU
@@ -49,7 +50,7 @@ __device__ __forceinline__ int element_of(const LatticeGeom &g, const int (&x)[3
 }
 
 template <int WPT>
-__global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a)
+__global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a, int chunk)
 {
   __shared__ unsigned long long acc2[kMaxPairShells];
   __shared__ unsigned long long acc11[kMaxPairShells];
@@ -79,8 +80,8 @@ __global__ __launch_bounds__(kPairBlock) void k_pairs(PairArgs a)
       pci += (unsigned)__popcll(qi[q]);
     }
   }
-  const int d0 = (int)blockIdx.y * kPairChunk;
-  const int d1 = min(a.n_disp, d0 + kPairChunk);
+  const int d0 = (int)blockIdx.y * chunk;
+  const int d1 = min(a.n_disp, d0 + chunk);
   for (int dq = d0; dq < d1; ++dq) {
     const int4 dv = a.disp[dq];   // components, shell * 2 + whether it counts twice
     const int r2 = dv.w >> 1;
@@ -148,16 +149,18 @@ __global__ __launch_bounds__(kTileBlock) void k_pairs_tile(PairArgs a, int wpt)
 {
   extern __shared__ u64 pair_lds[];
   const int tid = (int)threadIdx.x;
-  const int L = a.g.L, h = a.halo, T = a.rows;
+  const int L = a.g.L, h = a.halo, T = a.tiles.rows;
   const int width = L + 2 * h, area = (T + 2 * h) * width;
   // word pairs in one 16-byte read (WC = 1: single words)
   constexpr int V = WC > 1 ? 2 : 1, G = WC / V;
   u64 *q = pair_lds;                                                  // [G][area][V]
   u64 *acc2 = q + (size_t)WC * area, *acc11 = acc2 + a.r2_max + 1;
   unsigned short *sum = reinterpret_cast<unsigned short *>(acc11 + a.r2_max + 1);   // [area]
-  const int y0 = (int)blockIdx.x * T, z = (int)blockIdx.y, dz = (int)blockIdx.z;
+  const int y0 = (int)blockIdx.x * T, z = (int)blockIdx.y, dz = (int)blockIdx.z / a.tiles.parts;
+  const int part = (int)blockIdx.z - dz * a.tiles.parts;
   const int zb = z + dz < L ? z + dz : z + dz - L;
-  const int d0 = a.start[dz], d1 = a.start[dz + 1];
+  const int first = a.start[dz], listed = a.start[dz + 1] - first;   // at most 2^13 displacements in a plane
+  const int d0 = first + listed * part / a.tiles.parts, d1 = first + listed * (part + 1) / a.tiles.parts;
   if (d0 == d1) return;
   for (int k = tid; k <= a.r2_max; k += kTileBlock) acc2[k] = acc11[k] = 0;
   // this thread's sites: tile positions tid + k * kTileBlock (rows beyond the lattice hold none)
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(kTileBlock) void k_pairs_tile(PairArgs a, int wpt)
         }
         if (w0 == 0) c11 += __umul24(p[k], (unsigned)sum[j]);   // both at most 1024
       }
-      if (!dv.w && run < 16) continue;
+      if (!dv.w && run < 16 && d + 1 < d1) continue;
       c2 = wave_sum_last(c2);
       if (w0 == 0) c11 = wave_sum_last(c11);
       if (__lane_id() == 63) {
@@ -301,24 +304,66 @@ hipError_t launch_pairs_graph(const PairGraphArgs &a, int wpt, hipStream_t s)
   return hipGetLastError();
 }
 
-bool pairs_tile_rows(int L, int halo, int r2_max, int *rows, int *words)
+// Displacements of a gather workgroup: fewer while that leaves CUs idle.
+static int gather_chunk(const LatticeGeom &g, int n_disp)
 {
-  if (L > kTileSites * kTileBlock) return false;
-  const int T = std::min(L, kTileSites * kTileBlock / L);
-  for (int wc = 4; wc >= 1; wc /= 2)
-    if (tile_lds(L, halo, T, r2_max, wc) <= kTileLds) {
-      *rows = T;
-      *words = wc;
-      return true;
-    }
-  return false;
+  int chunk = kPairChunk;
+  while (chunk > 8 && (int64_t)((g.N + kPairBlock - 1) / kPairBlock) * ((n_disp + chunk - 1) / chunk) < 256) chunk /= 2;
+  return chunk;
 }
 
-hipError_t launch_pairs_tile(const PairArgs &a, int wpt, int words, hipStream_t s)
+// Microseconds of either kernel beyond what they share, fitted to L = 8 to 512 in 2D and 4 to 64 in 3D,
+// 1 to 16 words, squared radii 0 to 2048 (within 10% for the gathers and 25% for the tiles).  A workgroup of
+// the gathers takes up to 32 displacements of 256 sites; one of the tiles loads its tile and then takes its
+// part of the displacements, so that more parts fill the device and cost more loads.
+// A call, tiles in one part -> as chosen here: 2D L = 64 x 1024 replicas to r2 = 400 2423 -> 149 us (gathers),
+// L = 64 x 64 236 -> 57 us (tiles in 64 parts; gathers 83); 3D L = 64 x 256 to r2 = 36, where one part fills the
+// device, 208 us (two parts 255, gathers 868).
+static double gather_us(const LatticeGeom &g, int W, int n_disp)
 {
-  const size_t lds = tile_lds(a.g.L, a.halo, a.rows, a.r2_max, words);
-  if (a.rows < 1 || a.rows * a.g.L > kTileSites * kTileBlock || 2 * a.halo > a.g.L || lds > kTileLds) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)((a.g.L + a.rows - 1) / a.rows), (unsigned)(a.g.d == 3 ? a.g.L : 1), (unsigned)(a.g.d == 3 ? a.halo + 1 : 1));
+  const int chunk = gather_chunk(g, n_disp);
+  const double blocks = (double)((g.N + kPairBlock - 1) / kPairBlock) * ((n_disp + chunk - 1) / chunk);
+  const double each = std::min(n_disp, chunk);
+  return each * (0.10 * W + 0.78) + 0.03 * W + blocks / 906.0 * each * (1.0 + 0.138 * W);
+}
+
+static double tile_us(const LatticeGeom &g, int W, int halo, int n_disp, int r2_max, const PairTiles &t)
+{
+  const int planes = g.d == 3 ? halo + 1 : 1;
+  const double area = (double)(t.rows + 2 * halo) * (g.L + 2 * halo) / 1024.0;
+  const double passes = (W + t.words - 1) / t.words;
+  const double listed = ((n_disp + planes - 1) / planes + t.parts - 1) / t.parts;
+  const double blocks = (double)((g.L + t.rows - 1) / t.rows) * (g.d == 3 ? g.L : 1) * planes * t.parts;
+  const double at_once = 256.0 * std::min<size_t>(2, (160 << 10) / tile_lds(g.L, halo, t.rows, r2_max, t.words));
+  return ((1.45 * passes + 0.80 * W) * area + 0.16 * listed * W + 2.1 * passes) * (1.0 + 1.54 * std::max(0.0, blocks / at_once - 1.0));
+}
+
+PairTiles pairs_tiles(const LatticeGeom &g, int W, int halo, int n_disp, int r2_max)
+{
+  PairTiles best{0, 0, 0};
+  if (g.L > kTileSites * kTileBlock) return best;
+  PairTiles t{std::min(g.L, kTileSites * kTileBlock / g.L), 4, 1};
+  while (t.words >= 1 && tile_lds(g.L, halo, t.rows, r2_max, t.words) > kTileLds) t.words /= 2;
+  if (t.words < 1) return best;
+  double least = gather_us(g, W, n_disp);
+  const int listed = n_disp / (g.d == 3 ? halo + 1 : 1);
+  for (; t.parts <= 64 && (t.parts == 1 || 2 * t.parts <= listed); t.parts *= 2) {
+    const double us = tile_us(g, W, halo, n_disp, r2_max, t);
+    if (us >= least) continue;
+    least = us;
+    best = t;
+  }
+  return best;
+}
+
+hipError_t launch_pairs_tile(const PairArgs &a, int wpt, hipStream_t s)
+{
+  const int rows = a.tiles.rows, words = a.tiles.words;
+  const size_t lds = tile_lds(a.g.L, a.halo, rows, a.r2_max, words);
+  if (rows < 1 || a.tiles.parts < 1 || rows * a.g.L > kTileSites * kTileBlock || 2 * a.halo > a.g.L || lds > kTileLds)
+    return hipErrorInvalidValue;
+  const dim3 grid((unsigned)((a.g.L + rows - 1) / rows), (unsigned)(a.g.d == 3 ? a.g.L : 1),
+                  (unsigned)((a.g.d == 3 ? a.halo + 1 : 1) * a.tiles.parts));
 #define KA_PT(WC)                                                                                        \
   do {                                                                                                   \
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_pairs_tile<WC>),           \
@@ -335,11 +380,12 @@ hipError_t launch_pairs_tile(const PairArgs &a, int wpt, int words, hipStream_t 
 
 hipError_t launch_pairs(const PairArgs &a, int wpt, hipStream_t s)
 {
-  const dim3 grid((unsigned)((a.g.N + kPairBlock - 1) / kPairBlock), (unsigned)((a.n_disp + kPairChunk - 1) / kPairChunk));
+  const int chunk = gather_chunk(a.g, a.n_disp);
+  const dim3 grid((unsigned)((a.g.N + kPairBlock - 1) / kPairBlock), (unsigned)((a.n_disp + chunk - 1) / chunk));
   if (wpt == 2)
-    hipLaunchKernelGGL((k_pairs<2>), grid, dim3(kPairBlock), 0, s, a);
+    hipLaunchKernelGGL((k_pairs<2>), grid, dim3(kPairBlock), 0, s, a, chunk);
   else
-    hipLaunchKernelGGL((k_pairs<1>), grid, dim3(kPairBlock), 0, s, a);
+    hipLaunchKernelGGL((k_pairs<1>), grid, dim3(kPairBlock), 0, s, a, chunk);
   return hipGetLastError();
 }
 
