@@ -136,18 +136,19 @@ struct Cube {
   template <int MU, int R, bool GIVEN>
   __device__ __forceinline__ void work_xy(u64 (&r)[8], const CubeDraw &g, int c, int m)
   {
-    u64 x[4][11];
-    gather<MU, R, 0>(x[0]);
-    gather<MU, R, 1>(x[1]);
-    gather<MU, R, 2>(x[2]);
-    gather<MU, R, 3>(x[3]);
     if constexpr (!GIVEN) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const uint32_t a = (uint32_t)((R + 2 * (q & 1)) & 3);
         r[q] = g.draw(c, MU == 0 ? a : (uint32_t)q, MU == 0 ? (uint32_t)q : a, (uint32_t)MU);
       }
+      __builtin_amdgcn_sched_barrier(0);   // the draws end before the gathered words take registers
     }
+    u64 x[4][11];
+    gather<MU, R, 0>(x[0]);
+    gather<MU, R, 1>(x[1]);
+    gather<MU, R, 2>(x[2]);
+    gather<MU, R, 3>(x[3]);
     exchange<MU, R, 0>(x[0], r[0], m);
     exchange<MU, R, 1>(x[1], r[1], m);
     exchange<MU, R, 2>(x[2], r[2], m);
@@ -203,6 +204,7 @@ struct Cube {
       r[2 * Y + 1] = g.draw(c, e0 + 2, Y, 2);
       r[2 * Y + 2] = g.draw(c, e1, Y + 1, 2);
       r[2 * Y + 3] = g.draw(c, e1 + 2, Y + 1, 2);
+      __builtin_amdgcn_sched_barrier(0);
     }
     u64 x[4][11];
     gather_z<e0, Y>(x[0]);
@@ -286,10 +288,10 @@ __global__ __launch_bounds__(256) void k_cube_accept(SquareArgs a)
 // Every class has its own code, with both places that its edges can take: with loops over the
 // classes, a quarter of the code, a sweep of L = 20 took 19.4 instead of 15.1 us.
 template <int P, bool GIVEN>   // 64 or 128 positions of LDS: 256 or 512 threads
-__global__ __launch_bounds__(4 * P) void k_cube_resident(SquareArgs a, int m)
+__global__ __launch_bounds__(4 * P, 2) void k_cube_resident(SquareArgs a, int m)
 {
   __shared__ u64 lds[64 * P];
-  const int word = (int)blockIdx.x;
+  const int word = xcd_remap((int)blockIdx.x, (int)gridDim.x);   // the words of a pair, whose state interleaves, in one XCD's L2
   const int slot = (int)threadIdx.x % P;
   // z mod 4 of this wave: residues 0, 2, 1, 3 in wave order
   const int g4 = __builtin_amdgcn_readfirstlane((int)threadIdx.x / P);
@@ -372,6 +374,7 @@ __global__ __launch_bounds__(4 * P) void k_cube_resident(SquareArgs a, int m)
   observe((int64_t)a.t0);
   const bool odd = az & 1;
   for (int s = 0; s < a.n_sweeps; ++s) {
+    if constexpr (!GIVEN) asm volatile("" : "+v"(g.site));   // else the products of all ids are kept (spilled) over the sweeps
     // One class: the work at the places of this wave's z, the words of the class D later, the
     // barrier, and the words that other threads changed.  Those are read before the next barrier,
     // so the next class must not write them from another thread.  One pair of classes does: after

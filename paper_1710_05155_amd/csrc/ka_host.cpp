@@ -826,9 +826,10 @@ int64_t block_acc_plan(int d, int64_t P, int W, size_t *bytes)
   const size_t per_sweep = (size_t)(d == 2 ? 256 : 1536) * (size_t)P * (size_t)W;
   if (per_sweep > kLdsAccBudget || (d == 3 && !block_resident(d, P))) return 0;
   const int64_t sweeps = std::min<int64_t>(5461, (int64_t)(kLdsAccBudget / per_sweep));   // grid limit of the draws
-  // two launches for one or two sweeps of a small 2D lattice cost more than its draws (L = 64 x 4096
-  // replicas: 11.7 against 9.0 us per sweep); in 3D the draws are dearer (L = 20 x 1024: 26 against 31)
-  if (d == 2 && block_resident(d, P) && sweeps < 3) return 0;
+  // On register blocks, two launches for one or two sweeps cost more than their draws: L = 64 x 4096 replicas
+  // 9.9 against 7.7 us per sweep, 3D L = 20 x 2048 35 against 24; at three, L = 48 x 4096 (7.0, 7.5), and
+  // five, 3D L = 16 x 1024 (14.4, 19.5), they pay.
+  if (block_resident(d, P) && !(d == 3 && P < ka::kCubeMinP) && sweeps < 3) return 0;
   if (bytes) *bytes = (size_t)sweeps * per_sweep;
   return sweeps;
 }

@@ -143,17 +143,18 @@ struct Square {
     constexpr int C = 4 * MU + R;
     constexpr bool GIVEN = D > 0;
     u64 (&rc)[4] = r[GIVEN ? C % (D ? D : 1) : 0];
-    u64 x[4][7];
-    gather<MU, R, 0>(x[0]);
-    gather<MU, R, 1>(x[1]);
-    gather<MU, R, 2>(x[2]);
-    gather<MU, R, 3>(x[3]);
     if constexpr (!GIVEN) {
       rc[0] = square_draw<MU, R, 0>(g);
       rc[1] = square_draw<MU, R, 1>(g);
       rc[2] = square_draw<MU, R, 2>(g);
       rc[3] = square_draw<MU, R, 3>(g);
+      __builtin_amdgcn_sched_barrier(0);   // the draws end before the gathered words take registers
     }
+    u64 x[4][7];
+    gather<MU, R, 0>(x[0]);
+    gather<MU, R, 1>(x[1]);
+    gather<MU, R, 2>(x[2]);
+    gather<MU, R, 3>(x[3]);
     exchange<MU, R, 0>(x[0], rc[0], m);
     exchange<MU, R, 1>(x[1], rc[1], m);
     exchange<MU, R, 2>(x[2], rc[2], m);
@@ -235,12 +236,16 @@ __device__ __forceinline__ void load_block(Square<P> &t, const SquareArgs &a, in
     for (int x = 0; x < 4; ++x) t.s[(x + 4 * y) * P + to] = t.n[y][x];
 }
 
-// Bound by issue and latency on one CU per word (0.44 us per class at 256 blocks).
+// Bound by issue and latency on one CU per word (0.44 us per class at 256 blocks).  The words of a
+// pair, whose state interleaves, meet in one XCD's L2.  Two waves a SIMD, so that beyond 256 words a CU works
+// on two: with draws among the gathers, and the products of every edge's id kept over the sweeps, a
+// thread took 311 registers and a CU held one.  20 sweeps, before -> now: L = 64 x 24576 replicas 322 ->
+// 212 us, L = 88 x 16384 265 -> 223; one sweep with its call L = 64 x 16384 41 -> 26.
 template <int NT, bool GIVEN>
-__global__ __launch_bounds__(NT) void k_square_resident(SquareArgs a, int m)
+__global__ __launch_bounds__(NT, 2) void k_square_resident(SquareArgs a, int m)
 {
   extern __shared__ u64 sq_lds[];
-  const int word = (int)blockIdx.x;
+  const int word = xcd_remap((int)blockIdx.x, (int)gridDim.x);
   const int pos = (int)threadIdx.x;
   // threads that fill the last wave run a block of their own of zeros, with itself as neighbour
   const bool mine = pos < a.g.P;
@@ -304,6 +309,7 @@ __global__ __launch_bounds__(NT) void k_square_resident(SquareArgs a, int m)
   };
   observe((int64_t)a.t0);
   for (int s = 0; s < a.n_sweeps; ++s) {
+    if constexpr (!GIVEN) asm volatile("" : "+v"(g.site));   // else the products of all ids are kept (spilled) over the sweeps
     t.template sweep<D>(r, g, m, s + 1 < a.n_sweeps);
     g.acc += 32u * (size_t)a.g.P;
     g.t += 1;

@@ -51,6 +51,7 @@ void launch(dim3 grid, dim3 block, const std::function<void()> &kernel);
 #define hipLaunchKernelGGL(kernel, grid, block, lds, stream, ...) cpu::launch(grid, block, [&] { kernel(__VA_ARGS__); })
 
 #define __builtin_amdgcn_readfirstlane(x) (x)
+#define __builtin_amdgcn_sched_barrier(x)
 #define __builtin_amdgcn_bitop3_b32(a, b, c, table) cpu::bitop3(a, b, c, table)
 namespace cpu {
 inline uint32_t bitop3(uint32_t a, uint32_t b, uint32_t c, uint32_t table)

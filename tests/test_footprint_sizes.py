@@ -18,7 +18,7 @@ def allocated(d, L, W):
         return total
     per_sweep = (4 * 8 if d == 2 else 16 * 12) * P * W * 8   # edges of a sweep x words
     sweeps = min(5461, 8 * MIB // per_sweep)
-    if sweeps >= (3 if d == 2 and resident else 1):
+    if sweeps >= (3 if resident and P >= (1 if d == 2 else 64) else 1):
         total += sweeps * per_sweep
     row = 2 * N * W * 8
     total += 4 * MIB // row * row if resident else N * W * 8

@@ -6,6 +6,7 @@ word, before or after it, then sees the wrong side in one of the two."""
 import ctypes
 import functools
 import os
+import re
 import shutil
 import subprocess
 
@@ -28,7 +29,7 @@ def lib(tmp_path_factory):
         with open(os.path.join(CSRC, name + ".hip")) as fh:
             text = fh.read()
         text = text.replace("extern __shared__ u64 sq_lds[];", "u64 *sq_lds = reinterpret_cast<u64 *>(cpu::dynamic_lds);")
-        text = text.replace('asm volatile("" : "+s"(to));', "")   # a scalar register: no such thing here
+        text = re.sub(r'asm volatile\("" : "\+[sv]"\(\S+\)\);', ";", text)   # names register files that are not here
         sources.append(str(out / (name + ".cpp")))
         with open(sources[-1], "w") as fh:
             fh.write(text)
