@@ -598,6 +598,24 @@ bool capturing(const ka_sim *s)
 // A lattice that one workgroup per word holds on register blocks.
 bool block_resident(int d, int64_t P) { return P <= (d == 2 ? ka::kSquareResidentP : ka::kCubeResidentP); }
 
+// A lattice whose plane of n and f a workgroup keeps in LDS, a thread per edge of a class, instead of register
+// blocks, a thread per 16 sites.  A thread's four edges in turn take longer than one where the words
+// are drawn ahead in 3D (L = 12 x 64 replicas 8.1 against 11.1 us per sweep), and where they are drawn in the sweep,
+// with the Philox call of each shared by a pair of words.  In 2D that is where drawing ahead stops paying (see
+// block_acc_plan), about at W L = 4000, and up to L = 40, or to 48 with more words than CUs: microseconds
+// per sweep in LDS and on blocks, L = 12 x 24576 replicas 4.4 and 4.9 (x 16384: 4.4 and 4.1), L = 24 x 12288 5.1 and
+// 5.4 (x 8192: 5.1 and 4.5), L = 40 x 8192 6.7 and 7.2 (x 6144: 6.7 and 6.5), L = 48 x 24576 8.7 and 10.0
+// (x 16384: 8.7 and 7.7), L = 56 x 24576 10.4 and 10.7; 3D L = 16 x 24576 21 and 26 (x 16384: 20.6 and 19.9).
+// With an odd number of words a workgroup holds one: 3D L = 16 x 12352 17.0 and 20.3, and 2D L = 92 and 96 fit
+// (18.6 at up to 256 words, on tiles 16 at 33 words, 20 at 64, 41 at 193).
+bool block_in_lds(int d, int64_t P, int W)
+{
+  const bool odd = W % 2 != 0;
+  if (d == 3) return P < ka::kCubeMinP || (P == ka::kCubeMinP && W > (odd ? 28 : 256));
+  if (P > ka::kSquareResidentP) return odd && P <= 576 && W >= 61;
+  return P >= 9 && (P <= 100 || (P <= 144 && W > 256)) && P * W * W >= 1000000;
+}
+
 Route route(const ka_sim *s)
 {
   if (!s->lattice) return use_lds(s) ? Route::lds : Route::passes;
@@ -606,7 +624,7 @@ Route route(const ka_sim *s)
   // Options that arrange class passes keep them (they have no effect on a sim whose word plane
   // fits in LDS).
   if (!use_lds(s) && (s->plane_streams || s->plane_group_opt >= 0 || s->timing_every > 0)) return Route::passes;
-  if (s->geom.d == 3 && s->geom.P < ka::kCubeMinP) return Route::lds;
+  if (block_in_lds(s->geom.d, s->geom.P, s->W) && s->lds_fits) return Route::lds;
   // A capture cannot allocate, nor can its replays swap the two copies of n; and once a graph holds
   // n's address, n stays there.
   if (capturing(s) && !(small && use_lds(s))) return Route::passes;
@@ -826,10 +844,14 @@ int64_t block_acc_plan(int d, int64_t P, int W, size_t *bytes)
   const size_t per_sweep = (size_t)(d == 2 ? 256 : 1536) * (size_t)P * (size_t)W;
   if (per_sweep > kLdsAccBudget || (d == 3 && !block_resident(d, P))) return 0;
   const int64_t sweeps = std::min<int64_t>(5461, (int64_t)(kLdsAccBudget / per_sweep));   // grid limit of the draws
-  // On register blocks, two launches for one or two sweeps cost more than their draws: L = 64 x 4096 replicas
-  // 9.9 against 7.7 us per sweep, 3D L = 20 x 2048 35 against 24; at three, L = 48 x 4096 (7.0, 7.5), and
-  // five, 3D L = 16 x 1024 (14.4, 19.5), they pay.
-  if (block_resident(d, P) && !(d == 3 && P < ka::kCubeMinP) && sweeps < 3) return 0;
+  // Two launches for few sweeps cost more than their draws.  On register blocks, for one or two: L = 64 x 4096
+  // replicas 9.9 against 7.7 us per sweep, 3D L = 20 x 2048 35 against 24; at three, L = 48 x 4096 (7.0, 7.5), and
+  // five, 3D L = 16 x 1024 (14.4, 19.5), they pay.  In LDS, where a thread draws for one edge, for fewer than ten: L = 8
+  // x 6144 (7 sweeps) 10.0 and 9.3, x 2048 (21) 9.0 and 9.1, L = 12 x 2048 (6) 13.6 and 12.6, x 1024 (12) 12.2 and
+  // 12.6; the one wave of L = 4 draws too slowly (x 65536, 5 sweeps: 11.8 and 13.7).
+  const bool lds = block_in_lds(d, P, W);
+  if (lds && d == 2) return 0;
+  if (block_resident(d, P) && sweeps < (lds && P > 1 ? 10 : 3)) return 0;
   if (bytes) *bytes = (size_t)sweeps * per_sweep;
   return sweeps;
 }
@@ -978,7 +1000,7 @@ hipError_t launch_lds(ka_sim *s, int64_t t_from, int64_t t_to, int q0, int q1, b
   a.key0 = (uint32_t)s->seed;
   a.key1 = (uint32_t)(s->seed >> 32);
   a.noise = s->noise;
-  if (s->lds_acc && a.n_sweeps > 0) {
+  if (s->lds_acc && a.n_sweeps > 0 && !(s->lattice && s->geom.d == 2)) {   // (in 2D those are register blocks')
     if (a.n_sweeps > s->lds_acc_sweeps) return hipErrorInvalidValue;
     a.acc = s->lds_acc;
     if (!s->lattice) a.acc_slots = ka::lds_graph_slots(max_class_edges(s->plan->class_start));
@@ -1078,29 +1100,60 @@ Route sweep_route(ka_sim *s)
   return by;
 }
 
-// ka_run on the resident path: chunks [a, b) of at most lds_chunk sweeps and at most as many
-// observations as the snapshot buffer holds; those due where a chunk starts with no sweep before
-// them count the state itself.
-hipError_t run_resident(ka_sim *s, const int64_t *obs_times, int n_obs)
+// Snapshot rows of a sim within their budget, and whether observations in LDS are counted in the loop by
+// their one workgroup instead: where few rows mean a launch for every few observations, and the workgroups
+// fit the device at once.  40 sweeps, each observed, by launches and in the loop: 2D L = 40 x 6144 replicas (1 row) 1304
+// and 1084 us, L = 24 x 16384 (1) 2067 and 1794, x 8192 (3) 1062 and 1056, x 4096 (7) 625 and 724, L = 48 x 2112 (3) 583
+// and 692, L = 32 x 24640 (none) 2877 and 2888, L = 64 x 8192 (none) 1701 and 1895, x 12352 2067 and 1838; 3D L = 12 x
+// 6144 (1) 1631 and 1333, x 4096 (2) 1188 and 1184, L = 16 x 1024 (4) 842 and 1593.
+size_t snap_fit(const ka_sim *s) { return kLdsSnapBudget / lds_snap_row_bytes(s->N, s->R); }
+
+bool count_in_loop(const ka_sim *s, int n_obs)
+{
+  const size_t fit = snap_fit(s);
+  if ((size_t)n_obs <= fit || s->W > 256) return false;
+  if (s->geom.d == 3) return fit <= 2;
+  return fit <= 3 && s->W >= 96 && (s->geom.L <= 48 || (s->wpt == 1 && s->W >= 128));
+}
+
+// Route of a ka_run: where register blocks would need such launches, and the observations are dense, the LDS
+// sweep, which counts in its loop, takes their place (2D L = 48 x 12352 replicas 1895 and 1580 us, 3D L = 16 x 16384
+// 3429 and 3039; every third sweep observed, 2475 and 2156, 4939 and 4766, but L = 48 x 8192 2053 and 2111).
+Route run_route(ka_sim *s, const int64_t *obs_times, int n_obs)
+{
+  const Route by = sweep_route(s);
+  if (by != Route::resident || !count_in_loop(s, n_obs) || obs_times[n_obs - 1] - s->t >= 3ll * n_obs) return by;
+  return s->lds_fits && ka::lds_lattice_supported(s->geom.d, s->geom.P, s->wpt) ? Route::lds : by;
+}
+
+// ka_run of a lattice in one workgroup per word or plane: chunks [a, b) of at most lds_chunk sweeps and, unless they
+// are counted in the loop, at most as many observations as the snapshot buffer holds; those due where a
+// chunk starts with no sweep before them count the state itself.
+hipError_t run_in_workgroup(ka_sim *s, Route by, const int64_t *obs_times, int n_obs)
 {
   hipError_t e = hipSuccess;
-  const int64_t chunk = lds_chunk(s);
-  const size_t fit = kLdsSnapBudget / lds_snap_row_bytes(s->N, s->R);
-  const int rows = ensure_lds_snap(s, std::min<size_t>(fit, (size_t)n_obs)) ? (int)std::min<size_t>(fit, (size_t)n_obs) : 0;
+  if (by == Route::lds) e = hipMemcpyAsync(s->obs_d, obs_times, (size_t)n_obs * sizeof(int64_t), hipMemcpyHostToDevice, s->stream);
+  const bool in_loop = by == Route::lds && count_in_loop(s, n_obs);
+  const auto launch = [&](int64_t from, int64_t to, int q0, int q1) {
+    return by == Route::lds ? launch_lds(s, from, to, q0, q1, !in_loop) : launch_resident(s, from, to, obs_times, q0, q1);
+  };
+  const int64_t chunk = by == Route::lds && s->geom.d == 2 ? kLdsChunk : lds_chunk(s);
+  const int want = (int)std::min<size_t>(snap_fit(s), (size_t)n_obs);
+  const int rows = in_loop ? n_obs : ensure_lds_snap(s, (size_t)want) ? want : 0;
   int64_t a = s->t;
   for (int q = 0; q < n_obs && e == hipSuccess;) {
     int q1 = q;
     while (q1 < n_obs && obs_times[q1] == a) ++q1;
     const int64_t last = obs_times[n_obs - 1];
     if (q1 > q && (rows == 0 || q1 - q >= rows || last == a)) {
-      e = launch_resident(s, a, a, obs_times, q, q1);
+      e = launch(a, a, q, q1);
       q = q1;
       continue;
     }
     int64_t b = std::min(a + chunk, rows > 0 ? last : obs_times[q]);
     while (rows > 0 && q1 < n_obs && obs_times[q1] <= b && q1 - q < rows) ++q1;
     if (rows > 0 && q1 < n_obs && obs_times[q1] <= b) b = obs_times[q1 - 1];   // the buffer is full there
-    e = launch_resident(s, a, b, obs_times, q, q1);
+    e = launch(a, b, q, q1);
     q = q1;
     a = b;
   }
@@ -1432,12 +1485,8 @@ extern "C" int ka_sweep(ka_sim *s, int64_t n_sweeps)
       int64_t done = 0;
       while (done < n_sweeps && e == hipSuccess) {
         const int64_t chunk = std::min(lds_chunk(s), n_sweeps - done);
-        if (by == Route::resident) {
-          e = launch_resident(s, s->t + done, s->t + done + chunk, nullptr, 0, 0);
-        } else {
-          e = ensure_obs_buffers(s, 1);
-          if (e == hipSuccess) e = launch_lds(s, s->t + done, s->t + done + chunk, 0, 0, false);
-        }
+        e = by == Route::resident ? launch_resident(s, s->t + done, s->t + done + chunk, nullptr, 0, 0)
+                                  : launch_lds(s, s->t + done, s->t + done + chunk, 0, 0, false);
         done += chunk;
       }
     } else {
@@ -1469,12 +1518,12 @@ extern "C" int ka_run(ka_sim *s, const int64_t *obs_times, int n_obs, int64_t *d
     const size_t cbytes = (size_t)n_obs * 3u * (size_t)s->R * sizeof(unsigned long long);
     e = hipMemsetAsync(s->counts, 0, cbytes, s->stream);
     const bool sweeps = prev > s->t;
-    const Route by = sweeps ? sweep_route(s) : Route::passes;
+    const Route by = sweeps ? run_route(s, obs_times, n_obs) : Route::passes;
     if (e == hipSuccess && !sweeps) {
       // counts of the state as it is: none of the buffers that sweeps take
       e = observe_rows(s, s->n, s->f, 0, 0, n_obs);
-    } else if (e == hipSuccess && by == Route::resident) {
-      e = run_resident(s, obs_times, n_obs);
+    } else if (e == hipSuccess && s->lattice && (by == Route::resident || by == Route::lds)) {
+      e = run_in_workgroup(s, by, obs_times, n_obs);
     } else if (e == hipSuccess && by == Route::lds) {
       e = hipMemcpyAsync(s->obs_d, obs_times, (size_t)n_obs * sizeof(int64_t), hipMemcpyHostToDevice, s->stream);
       // chunks [a, b) of at most lds_chunk sweeps; observation q goes to the first chunk

@@ -76,8 +76,7 @@ struct PassGraph {
   uint32_t c_end;
 };
 
-// Whole sweep loop of a general graph or a tiny 3D lattice inside one workgroup per plane (plane in
-// LDS).
+// Whole sweep loop of a general graph or a small lattice inside one workgroup per plane (plane in LDS).
 struct SweepLds {
   u64 *n;
   u64 *f;
@@ -101,7 +100,7 @@ struct SweepLds {
   int R;
   uint32_t key0, key1;
   // acceptance words of these sweeps generated beforehand (null: drawn in the loop).
-  // Lattices: element ((plane * n_sweeps + s) * C + c) * 16 P + edge of the class.
+  // 3D lattices: element ((plane * n_sweeps + s) * C + c) * 16 P + edge of the class.
   // Graphs: element (plane * n_sweeps + s) * E + k for class-sorted edge k (E = stride), and
   // acc_slots is the most edges any class gives one of the 1024 threads.
   u64 *acc;
@@ -202,6 +201,8 @@ hipError_t observe_scratch_setup(int device);
 unsigned long long *observe_scratch(int device);
 hipError_t launch_fill_u64(unsigned long long *p, int n, unsigned long long v, hipStream_t s);
 size_t sweep_lds_bytes(int N, int wpt);
+// Whether the LDS sweep has the edges of a lattice's class on its threads (P positions).
+bool lds_lattice_supported(int d, int P, int wpt);
 // Edge slots per thread of the LDS graph sweep for its largest class, and the most it takes
 // pre-generated acceptance words for.
 int lds_graph_slots(int max_class_edges);

@@ -1,5 +1,5 @@
-// ka_lds.hip -- LDS-resident sweep loop for general graphs whose word plane fits in LDS, and for 3D
-// lattices of fewer than kCubeMinP positions (gfx950).
+// ka_lds.hip -- LDS-resident sweep loop for general graphs whose word plane fits in LDS, for 3D
+// lattices of fewer than kCubeMinP positions, and for small lattices with many words (gfx950).
 //
 // Method: Boccagna, arXiv 1710.05155; the per-edge bit logic lives in ka_device.h.
 #include "ka_device.h"
@@ -106,6 +106,8 @@ __device__ void lds_observe_due(const SweepLds &a, const u64 *sn, const u64 *sf,
   }
 }
 
+constexpr int class_edges(int d, int P) { return (d == 2 ? 4 : 16) * P; }
+
 // Edge k of class c of a 3D lattice: the k / P-th lower-endpoint sublattice at position k % P.
 __device__ __forceinline__ Site class_edge(const LatticeGeom &g, int c, int k)
 {
@@ -113,7 +115,7 @@ __device__ __forceinline__ Site class_edge(const LatticeGeom &g, int c, int k)
   return decode(g, 3, class_sublattice(3, c >> 2, c & 3, q), k - q * g.P);
 }
 
-// Acceptance words of sweeps t0 .. t0 + n_sweeps - 1 for k_sweep_lds_lattice: one workgroup per
+// Acceptance words of sweeps t0 .. t0 + n_sweeps - 1 for k_sweep_lds_lattice in 3D: one workgroup per
 // (sweep, class) and plane, a thread per edge.  The words do not depend on the state, so the whole
 // device draws them ahead of the single-workgroup loop.
 template <int WPT>
@@ -122,19 +124,23 @@ __global__ __launch_bounds__(kLdsBlock) void k_lds_accept_lattice(SweepLds a)
   const int s = (int)blockIdx.x / a.C, c = (int)blockIdx.x - s * a.C;
   const int plane = (int)blockIdx.y;
   const int k = (int)threadIdx.x;
-  if (k >= 16 * a.g.P) return;
+  const int per_class = class_edges(3, a.g.P);
+  if (k >= per_class) return;
   const uint32_t e = (uint32_t)canonical(a.g, 3, class_edge(a.g, c, k)) * 3u + (uint32_t)(c >> 2);
   u64 r[WPT];
   accept_words<WPT>(a.t0 + (uint32_t)s, (uint32_t)c, e, plane, a.key0, a.key1, a.noise, r);
   Elem<WPT> v;
 #pragma unroll
   for (int w = 0; w < WPT; ++w) v.w[w] = r[w];
-  st<WPT>(a.acc, ((plane * a.n_sweeps + s) * a.C + c) * 16 * a.g.P + k, v);
+  st<WPT>(a.acc, ((plane * a.n_sweeps + s) * a.C + c) * per_class + k, v);
 }
 
-// A thread per edge of a class (at most 16 kCubeMinP of them), n and f in LDS.  With words drawn
-// ahead (GIVEN) those of the next class are loaded while this class is processed.
-template <int WPT, bool GIVEN>
+// A thread per edge of a class, n and f in LDS.  With words drawn ahead (GIVEN) those of the next class
+// are loaded while this class is processed.  Drawn in the loop, one Philox call serves both words of a pair.
+// SLOTS: edges a thread may have.  One in 2D up to L = 64, where the draw follows the state loads, which it covers
+// (L = 40 x 16384 6.7 us per sweep, 7.3 in the compiler's order); three beyond.  In 3D there is one, but code for
+// three comes out faster (L = 12 x 16384 12.7 against 13.3).
+template <int D, int WPT, bool GIVEN, int SLOTS>
 __global__ __launch_bounds__(kLdsBlock) void k_sweep_lds_lattice(SweepLds a, int m)
 {
   extern __shared__ u64 lds[];
@@ -145,43 +151,54 @@ __global__ __launch_bounds__(kLdsBlock) void k_sweep_lds_lattice(SweepLds a, int
   lds_load<WPT>(a, sn, sf, plane);
   int qo = 0;
   lds_observe_due<WPT>(a, sn, sf, plane, qo, (int64_t)a.t0, cnt);
-  const int k = (int)threadIdx.x;
-  const int per_class = 16 * a.g.P;
+  const int tid = (int)threadIdx.x;
+  const int per_class = class_edges(D, a.g.P);
+  static_assert(!GIVEN || SLOTS == 1, "one word ahead");
   // the division and the block coordinates are done once; per class only the residues change
-  const int q = k / a.g.P;
-  const Site site = decode(a.g, 3, 0, k - q * a.g.P);
+  int slot_q[SLOTS];
+  Site slot_site[SLOTS];
+#pragma unroll
+  for (int j = 0; j < SLOTS; ++j) {
+    const int k = tid + j * kLdsBlock;
+    slot_q[j] = k / a.g.P;
+    slot_site[j] = decode(a.g, D, 0, k - slot_q[j] * a.g.P);
+  }
   Elem<WPT> next;
-  if (GIVEN && k < per_class) next = ld<WPT>(a.acc, plane * a.n_sweeps * a.C * per_class + k);
+  if (GIVEN && tid < per_class) next = ld<WPT>(a.acc, plane * a.n_sweeps * a.C * per_class + tid);
   for (int s = 0; s < a.n_sweeps; ++s) {
     const uint32_t t = a.t0 + (uint32_t)s;
     for (int c = 0; c < a.C; ++c) {
       const int mu = c >> 2;
-      const int sub = class_sublattice(3, mu, c & 3, q);
-      Site si = site;
-      si.a[0] = sub & 3;
-      si.a[1] = (sub >> 2) & 3;
-      si.a[2] = (sub >> 4) & 3;
-      si.idx += sub * a.g.P;
       const Elem<WPT> rw = next;
       const int step = (plane * a.n_sweeps + s) * a.C + c + 1;
-      if (GIVEN && k < per_class && (c + 1 < a.C || s + 1 < a.n_sweeps)) next = ld<WPT>(a.acc, step * per_class + k);
-      const auto edge = [&](auto MU) {
-        int i, j, ii[5], jj[5];
-        uint32_t e;
-        lattice_edge_indices<3, decltype(MU)::value>(a.g, si, i, j, ii, jj, e);
-        edge_update_with<5, WPT>(sn, sf, i, j, ii, jj, m, [&](u64 (&r)[WPT]) {
-          if constexpr (GIVEN) {
+      if (GIVEN && tid < per_class && (c + 1 < a.C || s + 1 < a.n_sweeps)) next = ld<WPT>(a.acc, step * per_class + tid);
 #pragma unroll
-            for (int w = 0; w < WPT; ++w) r[w] = rw.w[w];
-          } else {
-            accept_words<WPT>(t, (uint32_t)c, e, plane, a.key0, a.key1, a.noise, r);
-          }
-        });
-      };
-      if (k < per_class) {
+      for (int j = 0; j < SLOTS; ++j) {
+        if (tid + j * kLdsBlock >= per_class) break;
+        const int sub = class_sublattice(D, mu, c & 3, slot_q[j]);
+        Site si = slot_site[j];
+        si.a[0] = sub & 3;
+        si.a[1] = (sub >> 2) & 3;
+        si.a[2] = (sub >> 4) & 3;
+        si.idx += sub * a.g.P;
+        const auto edge = [&](auto MU) {
+          constexpr int K = 2 * D - 1;
+          int i, n, ii[K], jj[K];
+          uint32_t e;
+          lattice_edge_indices<D, decltype(MU)::value>(a.g, si, i, n, ii, jj, e);
+          edge_update_with<K, WPT>(sn, sf, i, n, ii, jj, m, [&](u64 (&r)[WPT]) {
+            if constexpr (GIVEN) {
+#pragma unroll
+              for (int w = 0; w < WPT; ++w) r[w] = rw.w[w];
+            } else {
+              if constexpr (D == 2 && SLOTS == 1) __builtin_amdgcn_sched_barrier(0);
+              accept_words<WPT>(t, (uint32_t)c, e, plane, a.key0, a.key1, a.noise, r);
+            }
+          });
+        };
         if (mu == 0) edge(std::integral_constant<int, 0>());
         else if (mu == 1) edge(std::integral_constant<int, 1>());
-        else edge(std::integral_constant<int, 2>());
+        else if constexpr (D == 3) edge(std::integral_constant<int, 2>());
       }
       __syncthreads();
     }
@@ -296,6 +313,11 @@ hipError_t set_lds(Kern k, size_t bytes)
 
 }  // namespace
 
+bool lds_lattice_supported(int d, int P, int wpt)
+{
+  return class_edges(d, P) <= (d == 2 && wpt == 1 ? 3 : 1) * kLdsBlock;
+}
+
 size_t sweep_lds_bytes(int N, int wpt) { return (size_t)2 * (size_t)N * (size_t)wpt * 8u; }
 
 int lds_graph_slots(int max_class_edges) { return (max_class_edges + kLdsBlock - 1) / kLdsBlock; }
@@ -309,8 +331,9 @@ hipError_t launch_lds_accept(const SweepLds &a, bool lattice, int wpt, hipStream
 {
   const int planes = (a.R / 64) / wpt;
   if (lattice) {
-    if (!a.acc || a.n_sweeps < 1 || a.g.d != 3 || a.g.P >= kCubeMinP) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(a.n_sweeps * a.C), (unsigned)planes), block((unsigned)((16 * a.g.P + 63) / 64 * 64));
+    const int per_class = class_edges(a.g.d, a.g.P);
+    if (!a.acc || a.n_sweeps < 1 || a.g.d != 3 || per_class > kLdsBlock) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(a.n_sweeps * a.C), (unsigned)planes), block((unsigned)((per_class + 63) / 64 * 64));
     if (wpt == 2) hipLaunchKernelGGL((k_lds_accept_lattice<2>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_lds_accept_lattice<1>), grid, block, 0, s, a);
     return hipGetLastError();
@@ -341,18 +364,23 @@ hipError_t launch_sweep_lds(const SweepLds &a, bool lattice, int zdeg, int m, in
   dim3 block(kLdsBlock);
   hipError_t e = hipSuccess;
   if (lattice) {
-    if (a.g.d != 3 || a.g.P >= kCubeMinP) return hipErrorInvalidValue;
-    block.x = (unsigned)((16 * a.g.P + 63) / 64 * 64);   // fewer waves, cheaper barriers
-#define KA_LDS_L(W, G)                                                            \
+    const int per_class = class_edges(a.g.d, a.g.P);
+    const bool one = per_class <= kLdsBlock;
+    if (!lds_lattice_supported(a.g.d, a.g.P, wpt) || (a.acc && a.g.d != 3)) return hipErrorInvalidValue;
+    // fewer waves, cheaper barriers; all of them where they count observations
+    if (one && (a.n_obs == 0 || a.snap)) block.x = (unsigned)((per_class + 63) / 64 * 64);
+#define KA_LDS_L(D, W, G, S)                                                      \
   do {                                                                            \
-    e = set_lds(k_sweep_lds_lattice<W, G>, lds_bytes);                            \
+    e = set_lds(k_sweep_lds_lattice<D, W, G, S>, lds_bytes);                      \
     if (e == hipSuccess)                                                          \
-      hipLaunchKernelGGL((k_sweep_lds_lattice<W, G>), grid, block, lds_bytes, s, a, m); \
+      hipLaunchKernelGGL((k_sweep_lds_lattice<D, W, G, S>), grid, block, lds_bytes, s, a, m); \
   } while (0)
-    if (wpt == 2) {
-      if (a.acc) KA_LDS_L(2, true); else KA_LDS_L(2, false);
+    if (a.g.d == 2) {
+      if (wpt == 2) KA_LDS_L(2, 2, false, 1); else if (one) KA_LDS_L(2, 1, false, 1); else KA_LDS_L(2, 1, false, 3);
+    } else if (wpt == 2) {
+      if (a.acc) KA_LDS_L(3, 2, true, 1); else KA_LDS_L(3, 2, false, 3);
     } else {
-      if (a.acc) KA_LDS_L(1, true); else KA_LDS_L(1, false);
+      if (a.acc) KA_LDS_L(3, 1, true, 1); else KA_LDS_L(3, 1, false, 3);
     }
 #undef KA_LDS_L
     return e == hipSuccess ? hipGetLastError() : e;
