@@ -616,6 +616,13 @@ bool block_in_lds(int d, int64_t P, int W)
   return P >= 9 && (P <= 100 || (P <= 144 && W > 256)) && P * W * W >= 1000000;
 }
 
+// Class passes instead of tiles: at L = 92 to 100 every site lies in 4.4 to 3.7 of the nine tiles, which costs more than
+// eight passes once the tiles fill the device six times and while all words stay in the Infinity Cache.
+// Microseconds per sweep on tiles and by passes: L = 92 x 12288 replicas 39 and 34, x 16384 48 and 41, x 24576 70
+// and 65, x 8192 29.3 and 29.4; L = 100 x 12288 39.5 and 35.3, x 24576 71 and 81; L = 104 x 12288 39.2 and 38.0, x 16384 48.4
+// and 48.5.  With one word an element the passes are slower (L = 100 x 12352 42 and 50).
+bool passes_for_tiles(const ka_sim *s) { return s->geom.L <= 100 && s->wpt == 2 && s->W >= 160 && s->N * s->W <= 3400000; }
+
 Route route(const ka_sim *s)
 {
   if (!s->lattice) return use_lds(s) ? Route::lds : Route::passes;
@@ -628,7 +635,7 @@ Route route(const ka_sim *s)
   // A capture cannot allocate, nor can its replays swap the two copies of n; and once a graph holds
   // n's address, n stays there.
   if (capturing(s) && !(small && use_lds(s))) return Route::passes;
-  return small ? Route::resident : s->captured ? Route::passes : Route::tiles;
+  return small ? Route::resident : s->captured || passes_for_tiles(s) ? Route::passes : Route::tiles;
 }
 
 hipEvent_t pooled_event(ka_sim *s)
