@@ -1894,11 +1894,12 @@ hipError_t move_state(ka_sim *s, const StateStaging &st, u64 *state, uint64_t *h
   return e;
 }
 
-// Small states (three arrays within the kept staging): the three arrays in one copy and one wait,
-// through host memory of the call.  Six copies and waits of a few KiB cost more than the
-// reordering ever did on the host (layered graph of 320 vertices x 64 replicas, export and import:
-// 180 us with six, 114 with two; the host's reordering took 169).
-bool small_state(const ka_sim *s) { return 3 * s->N * s->W <= kStateKept; }
+// Small states: the three arrays in one copy and one wait, through host memory of the call.  Six copies
+// and waits of a few KiB cost more than the reordering ever did on the host (layered graph of 320 vertices x 64
+// replicas, export and import: 180 us with six, 114 with two; the host's reordering took 169; export of
+// 12800 words 53 us, 85 with three copies, 68 on the host).
+constexpr int64_t kStateSmall = 7 << 13;   // words of the three arrays
+bool small_state(const ka_sim *s) { return 3 * s->N * s->W <= kStateSmall; }
 
 hipError_t move_small_state(ka_sim *s, const StateStaging &st, uint64_t *const host[3], bool out)
 {
@@ -1949,7 +1950,7 @@ extern "C" int ka_get_state(ka_sim *s, uint64_t *n, uint64_t *n0, uint64_t *f, i
     if (n || n0 || f) {
       e = st.get(s, (int64_t)(small_state(s) ? 3 * words : words));
       if (e != hipSuccess) return fail(KA_ENOMEM, "state staging: %s", hipGetErrorString(e));
-      if (small_state(s)) {
+      if (small_state(s) && st.size >= (int64_t)(3 * words)) {
         e = move_small_state(s, st, outs, true);
         if (e != hipSuccess) return hip_fail(e, "ka_get_state copy");
         if (t) *t = s->t;
@@ -1984,9 +1985,9 @@ extern "C" int ka_set_state(ka_sim *s, const uint64_t *n, const uint64_t *n0, co
     hipError_t e = hipStreamSynchronize(s->stream);
     if (e != hipSuccess) return hip_fail(e, "ka_set_state");
     StateStaging st;
-    const bool small = small_state(s);
-    e = st.get(s, (small ? 3 : 1) * s->N * s->W);
+    e = st.get(s, (small_state(s) ? 3 : 1) * s->N * s->W);
     if (e != hipSuccess) return fail(KA_ENOMEM, "state staging: %s", hipGetErrorString(e));
+    const bool small = small_state(s) && st.size >= 3 * s->N * s->W;
     if (small) {
       uint64_t *const from[3] = {const_cast<uint64_t *>(n), const_cast<uint64_t *>(n0), const_cast<uint64_t *>(f)};
       e = move_small_state(s, st, from, false);
