@@ -127,7 +127,7 @@ __device__ __forceinline__ void rank_candidates(Select &s, int64_t need)
 {
   __syncthreads();
   const int nc = s.ncand;
-  for (int k = (int)threadIdx.x; k < nc; k += kSelBlock) {
+  for (int k = (int)threadIdx.x; k < nc; k += (int)blockDim.x) {
     const u64 us = s.cand_u[k];
     const int is = s.cand_i[k];
     int rank = 0;
@@ -175,7 +175,7 @@ __device__ void select_full(const InitArgs &a, int b, Select &s)
   __syncthreads();
   if (tid == 0) s.ncand = 0;
   __syncthreads();
-  for (int64_t i = tid; i < a.N; i += kSelBlock) {
+  for (int64_t i = tid; i < a.N; i += (int)blockDim.x) {
     const u64 u = site_key(a, (int)i, b);
     if (pbits != 0 && (u >> (64 - pbits)) != prefix) continue;
     const int slot = atomicAdd(&s.ncand, 1);
@@ -481,7 +481,9 @@ hipError_t launch_init(const InitArgs &args, int R, int wpt, hipStream_t s)
   hipLaunchKernelGGL(k_init_clear, dim3((unsigned)((2 * (size_t)R + 255) / 256)), dim3(256), 0, s, reinterpret_cast<unsigned *>(a.thr_u),
                      2 * R, a.err);
   if (a.N < kWindowMinN) {
-    in_parts(a, R, kGridX, [&](const InitArgs &p, unsigned n) { hipLaunchKernelGGL(k_init_select, dim3(n), dim3(kSelBlock), 0, s, p); });
+    // (ranking needs a thread per site: 2D L = 4 x 262144 replicas 2740 us with 1024 of them, 980 with 128)
+    const int threads = a.N <= kRankAll ? kRankAll : kSelBlock;
+    in_parts(a, R, kGridX, [&](const InitArgs &p, unsigned n) { hipLaunchKernelGGL(k_init_select, dim3(n), dim3((unsigned)threads), 0, s, p); });
     in_parts(a, words, kGridY, [&](const InitArgs &p, unsigned n) {
       const dim3 grid((unsigned)((a.N + 63) / 64), n);
       if (wpt == 2) hipLaunchKernelGGL((k_init_fill<2>), grid, dim3(kFillBlock), 0, s, p);

@@ -312,7 +312,8 @@ static int gather_chunk(const LatticeGeom &g, int n_disp)
   return chunk;
 }
 
-// Microseconds of either kernel beyond what they share, fitted to L = 8 to 512 in 2D and 4 to 64 in 3D,
+// Microseconds of either kernel beyond what they share (the tiles' estimate, the rougher one, has to be below
+// the other by a margin), fitted to L = 8 to 512 in 2D and 4 to 64 in 3D,
 // 1 to 16 words, squared radii 0 to 2048 (within 10% for the gathers and 25% for the tiles).  A workgroup of
 // the gathers takes up to 32 displacements of 256 sites; one of the tiles loads its tile and then takes its
 // part of the displacements, so that more parts fill the device and cost more loads.
@@ -345,7 +346,7 @@ PairTiles pairs_tiles(const LatticeGeom &g, int W, int halo, int n_disp, int r2_
   PairTiles t{std::min(g.L, kTileSites * kTileBlock / g.L), 4, 1};
   while (t.words >= 1 && tile_lds(g.L, halo, t.rows, r2_max, t.words) > kTileLds) t.words /= 2;
   if (t.words < 1) return best;
-  double least = gather_us(g, W, n_disp);
+  double least = 0.85 * gather_us(g, W, n_disp);
   const int listed = n_disp / (g.d == 3 ? halo + 1 : 1);
   for (; t.parts <= 64 && (t.parts == 1 || 2 * t.parts <= listed); t.parts *= 2) {
     const double us = tile_us(g, W, halo, n_disp, r2_max, t);
