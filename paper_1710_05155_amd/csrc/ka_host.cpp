@@ -886,12 +886,16 @@ int max_class_edges(const std::vector<int> &class_start)
   return most;
 }
 
+// A lattice sim draws its first sweeps in the loop: the buffer's allocation and release take as long as
+// drawing about ten ahead saves (a job of one sweep, 2D L = 88 x 128 replicas 190 us with the buffer, 160 without).
+constexpr int64_t kDrawAheadFrom = 10;
+
 // Sweeps per LDS-resident launch of this sim; when its layout takes pre-generated acceptance
-// words, allocates their buffer on first use (if that fails, and in a capture, which cannot
+// words, allocates their buffer (if that fails, and in a capture, which cannot
 // allocate, the words are drawn in the loop and launches cover up to kLdsChunk sweeps).
 int64_t lds_chunk(ka_sim *s)
 {
-  if (!s->lds_acc_tried && !capturing(s)) {
+  if (!s->lds_acc_tried && !capturing(s) && (!s->lattice || s->planned_sweeps >= kDrawAheadFrom)) {
     s->lds_acc_tried = true;
     size_t bytes = 0;
     const int64_t sweeps = s->lattice ? block_acc_plan(s->geom.d, s->geom.P, s->W, &bytes)
@@ -1487,6 +1491,7 @@ extern "C" int ka_sweep(ka_sim *s, int64_t n_sweeps)
     DeviceGuard dg(s->device);
     hipError_t e = hipSuccess;
     if (capturing(s)) s->captured = true;
+    s->planned_sweeps += n_sweeps;
     const Route by = sweep_route(s);
     if (by == Route::resident || by == Route::lds) {
       int64_t done = 0;
@@ -1525,6 +1530,7 @@ extern "C" int ka_run(ka_sim *s, const int64_t *obs_times, int n_obs, int64_t *d
     const size_t cbytes = (size_t)n_obs * 3u * (size_t)s->R * sizeof(unsigned long long);
     e = hipMemsetAsync(s->counts, 0, cbytes, s->stream);
     const bool sweeps = prev > s->t;
+    s->planned_sweeps += prev - s->t;
     const Route by = sweeps ? run_route(s, obs_times, n_obs) : Route::passes;
     if (e == hipSuccess && !sweeps) {
       // counts of the state as it is: none of the buffers that sweeps take

@@ -99,6 +99,7 @@ struct ka_sim {
   ka::u64 *lds_acc = nullptr;     // acceptance words drawn ahead (LDS graph sweep, register blocks)
   int64_t lds_acc_sweeps = 0;     // sweeps lds_acc holds (0: words drawn in the loop)
   bool lds_acc_tried = false;
+  int64_t planned_sweeps = 0;     // lattices: sweeps of all calls until lds_acc_tried
   ka::u64 *lds_snap = nullptr;    // LDS sweep: snapshots of n and f taken at observation times
   size_t lds_snap_rows = 0;       // snapshot rows lds_snap holds
   int64_t timing_every = 0;
