@@ -24,9 +24,8 @@ class PageToucher {
       try {
         threads_.emplace_back([base, a, b] {
           const auto touch = [base](size_t q) {
-            volatile char *const p = base + q;
-            const char held = *p;
-            *p = held;
+            char held = 0;   // writes 0 over 0 or what it found: one page fault, a read and a store take two
+            (void)__atomic_compare_exchange_n(base + q, &held, (char)0, false, __ATOMIC_RELAXED, __ATOMIC_RELAXED);
           };
           for (size_t q = a; q < b; q += 4096) touch(q);
           if (a < b) touch(b - 1);   // the last page of a part need not begin a multiple of 4096 after its start

@@ -1,5 +1,5 @@
 // Touches an array that holds values and one that was never written, both past the size from which
-// arrays are touched, and looks at every byte; writing the second then faults no page in.
+// arrays are touched, and looks at every byte; the second takes one fault a page, and writing it then none.
 // Argument: bytes beyond that size.
 #include <sys/mman.h>
 #include <sys/resource.h>
@@ -17,13 +17,19 @@ int main(int argc, char **argv)
   for (size_t k = 0; k < held.size(); ++k) held[k] = (unsigned char)(k * 37 + 11);
   unsigned char *fresh = static_cast<unsigned char *>(mmap(nullptr, bytes, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS, -1, 0));
   if (fresh == MAP_FAILED) return 2;
+  (void)madvise(fresh, bytes, MADV_NOHUGEPAGE);
+  rusage before, after;
   {
     PageToucher touch[2];
     touch[0].add(held.data() + 8, bytes);
-    touch[1].add(fresh, bytes);
     touch[0].wait();
+    getrusage(RUSAGE_SELF, &before);
+    touch[1].add(fresh, bytes);
   }
-  rusage before, after;
+  getrusage(RUSAGE_SELF, &after);
+  // (a thread's start and end take some of their own)
+  const long pages = (long)((bytes + 4095) / 4096);
+  if (after.ru_minflt - before.ru_minflt > pages + pages / 2) return std::printf("%ld faults for %ld pages\n", after.ru_minflt - before.ru_minflt, pages), 1;
   getrusage(RUSAGE_SELF, &before);
   volatile unsigned char *const w = fresh;
   for (size_t k = 0; k < bytes; k += 4096) w[k] = 0;
