@@ -201,11 +201,18 @@ int ka_sim_info(const ka_sim *s, int64_t *N, int *n_replicas, int64_t *K, int *m
  *                  Paths 0 and 2 run 2D lattices and 3D L = 16 and 20 on 4 x 4 blocks of
  *                  sites held in registers: the whole loop in one workgroup per word (2D up
  *                  to L = 88), larger 2D lattices one to three sweeps a launch on tiles of the
- *                  lattice (class passes while KA_OPT_TIMING, KA_OPT_PLANE_STREAMS or
- *                  KA_OPT_PLANE_GROUPS is set and the word plane does not fit in LDS, under
- *                  stream capture, and for the rest of a sim's life once a ka_sweep of it has
- *                  been captured: tiles move the state between two copies, and a captured sweep
- *                  keeps the address of one).
+ *                  lattice.  Small lattices with many words (2D up to L = 48, 3D L = 16) keep
+ *                  the plane in LDS instead, as 3D L = 4 to 12 always do, and so do 2D L = 92
+ *                  and 96 with 61 or more words, an odd number; 2D L = 92 to 100 with 160 or
+ *                  more words, an even number, run as class passes while N x words is at most
+ *                  3.4 million.  In place of tiles, class passes run while KA_OPT_TIMING,
+ *                  KA_OPT_PLANE_STREAMS or KA_OPT_PLANE_GROUPS is set and the word plane does
+ *                  not fit in LDS, under stream capture, and for the rest of a sim's life once
+ *                  a ka_sweep of it has been captured: tiles move the state between two
+ *                  copies, and a captured sweep keeps the address of one.
+ *                  From a sim's tenth sweep on, lattices of few words have their acceptance
+ *                  words drawn ahead into a buffer of up to 8 MiB, which a capture cannot
+ *                  allocate: one recorded earlier draws in its sweeps.
  *   KA_OPT_TIMING: k > 0 brackets every k-th class-pass launch with HIP events on the sim's
  *                  stream (for per-kernel durations, read with ka_timing); 0 = off.
  *   KA_OPT_NOISE:  0 (default) = an independent acceptance bit per replica, edge and sweep;
@@ -254,8 +261,9 @@ int ka_set_option(ka_sim *s, int option, int64_t value);
  * events and their summed duration in milliseconds (synchronises the stream). */
 int ka_timing(ka_sim *s, int64_t *launches, int64_t *timed, double *timed_ms);
 
-/* Path a ka_sweep would take now: 2 = resident in one workgroup (the word plane fits in LDS and
- * KA_OPT_PATH is not 1), 1 = otherwise. */
+/* Class of path: 2 = the word plane fits in the LDS of one workgroup and KA_OPT_PATH is not 1
+ * (also for 2D L = 92 and 96 with an odd number of words, which run on tiles while there are
+ * fewer than 61), 1 = otherwise. */
 int ka_sim_path(const ka_sim *s, int *path);
 
 /* Release a sim.  If the sim is still a batch member, its batch is first run to completion

@@ -11,8 +11,8 @@
 // words (and the moved-ever bits from the change) from LDS after the barrier.  The waves of residues 0
 // and 2, the active ones of every other such class, sit on different SIMDs.
 //
-// Bound by issue and latency on one CU per word.  Measured per sweep: L = 16 x 64 replicas 11.1 us
-// (13.6 with n and f in LDS), L = 20 x 64 15.1 (24), L = 20 x 256 17.6 (51 as class passes over global
+// Bound by issue and latency on one CU per word.  Measured per sweep: L = 16 x 64 replicas 10.8 us
+// (13.6 with n and f in LDS), L = 20 x 64 15.1 (24), L = 20 x 256 17.0 (51 as class passes over global
 // memory).  Below L = 16 the four edges of a thread in turn take longer than one edge per
 // thread (L = 12: 11.1 against 9.3 us, L = 8: 10.9 against 7.7), and the kernel of ka_lds.hip runs.
 #include "ka_device.h"

@@ -8,7 +8,7 @@
 // standard deviations sqrt(p (1 - p) / N), p = K/N, of p, so k_init_keys compares the keys with a
 // window around p: below it a site is occupied, above it empty, and the few sites inside are
 // listed per replica.  k_init_pick then finds the threshold among a replica's listed sites and
-// sets the bits of those at or below it.  A replica whose threshold falls outside the window (a few in 10^6)
+// sets the bits of those at or below it.  A replica whose threshold falls outside the window (about one in 10^5)
 // is selected by radix over all its keys instead, and its bits set site by site.
 #include <algorithm>
 #include <cmath>

@@ -136,7 +136,8 @@ struct SquareArgs {
 };
 // Positions (4 x 4 blocks) of a lattice that one workgroup holds.
 constexpr int kSquareResidentP = 512;
-// The same for 3D lattices in one workgroup per word (fewer positions than kCubeMinP: ka_lds.hip).
+// The same for 3D lattices in one workgroup per word (fewer positions than kCubeMinP, and kCubeMinP with many
+// words: ka_lds.hip).
 constexpr int kCubeResidentP = 128, kCubeMinP = 64;
 hipError_t launch_cube_accept(const SquareArgs &a, hipStream_t s);
 hipError_t launch_cube_resident(const SquareArgs &a, int m, hipStream_t s);

@@ -19,8 +19,8 @@
 // the first sweep, 8 in each one more).
 //
 // Measured per sweep, 64 replicas, against class passes over global memory (LDS-resident passes
-// for L = 64): L = 64 3.5 us (7.2), L = 128 6.3 us (25), L = 256 8.1 us (28), L = 512 12.3 us (28),
-// L = 1024 20 us (35), L = 4096 212 us (355); 256 replicas: L = 512 23 us (32), L = 4096 765 us
+// for L = 64): L = 64 3.4 us (7.2), L = 128 6.2 us (25), L = 256 8.2 us (28), L = 512 13.0 us (28),
+// L = 1024 20 us (35), L = 4096 177 us (355); 256 replicas: L = 512 22 us (32), L = 4096 680 us
 // (1600).  At 1024 threads (whole lattices up to L = 128, tiles of 128 x 128) the 128 registers a
 // thread may have do not hold a block, and the spills cost more than the halos save (L = 128: 30
 // us); tiles of 96 x 96 took longer at every size.
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(NT, 2) void k_square_resident(SquareArgs a, int m)
   extern __shared__ u64 sq_lds[];
   const int word = xcd_remap((int)blockIdx.x, (int)gridDim.x);
   const int pos = (int)threadIdx.x;
-  // threads that fill the last wave run a block of their own of zeros, with itself as neighbour
+  // threads that fill the last wave run a copy of block 0 with itself as neighbour, which is not stored
   const bool mine = pos < a.g.P;
   const int p = mine ? pos : 0;
   const int p1 = div_q(a.g, p), p0 = p - p1 * a.g.Q;
