@@ -210,9 +210,10 @@ int ka_sim_info(const ka_sim *s, int64_t *N, int *n_replicas, int64_t *K, int *m
  *                  not fit in LDS, under stream capture, and for the rest of a sim's life once
  *                  a ka_sweep of it has been captured: tiles move the state between two
  *                  copies, and a captured sweep keeps the address of one.
- *                  From a sim's tenth sweep on, lattices of few words have their acceptance
- *                  words drawn ahead into a buffer of up to 8 MiB, which a capture cannot
- *                  allocate: one recorded earlier draws in its sweeps.
+ *                  Lattices of few words have their acceptance words drawn ahead into a buffer
+ *                  of up to 8 MiB from a sim's tenth sweep on, or from its first ka_sweep where
+ *                  the word plane fits in LDS.  A capture cannot allocate it: one recorded
+ *                  before any direct ka_sweep draws in its sweeps.
  *   KA_OPT_TIMING: k > 0 brackets every k-th class-pass launch with HIP events on the sim's
  *                  stream (for per-kernel durations, read with ka_timing); 0 = off.
  *   KA_OPT_NOISE:  0 (default) = an independent acceptance bit per replica, edge and sweep;

@@ -888,6 +888,8 @@ int max_class_edges(const std::vector<int> &class_start)
 
 // A lattice sim draws its first sweeps in the loop: the buffer's allocation and release take as long as
 // drawing about ten ahead saves (a job of one sweep, 2D L = 88 x 128 replicas 190 us with the buffer, 160 without).
+// A direct ka_sweep of a sim whose captures run in one workgroup takes it at once, since a capture cannot (one sweep, then
+// a graph of 50: L = 64 x 64 203 us a replay with the buffer, 407 without).
 constexpr int64_t kDrawAheadFrom = 10;
 
 // Sweeps per LDS-resident launch of this sim; when its layout takes pre-generated acceptance
@@ -1491,7 +1493,7 @@ extern "C" int ka_sweep(ka_sim *s, int64_t n_sweeps)
     DeviceGuard dg(s->device);
     hipError_t e = hipSuccess;
     if (capturing(s)) s->captured = true;
-    s->planned_sweeps += n_sweeps;
+    s->planned_sweeps += n_sweeps > 0 && use_lds(s) && !capturing(s) ? std::max(n_sweeps, kDrawAheadFrom) : n_sweeps;
     const Route by = sweep_route(s);
     if (by == Route::resident || by == Route::lds) {
       int64_t done = 0;

@@ -29,3 +29,16 @@ def test_observation_takes_no_sweep_buffers(kind, size, R):
         for a, b in zip(rows, counts[1:]):
             assert (a[q] == b).all()
     s.free()
+
+
+# words drawn ahead would take 8 MiB
+@pytest.mark.parametrize("size,R", [((2, 64), 64), ((2, 88), 128), ((2, 104), 64), ((3, 20), 128)])
+def test_short_run_draws_in_its_sweeps(size, R):
+    g = ka.ka_graph_lattice(*size)
+    s = ka.ka_init(g, 2, 0.5, 1, R)
+    ka.ka_observe_noalloc(s)
+    before = free_bytes()
+    ka.ka_run(s, [1])
+    # three small buffers, each rounded up to 2 MiB at most
+    assert before - free_bytes() <= 6 << 20
+    s.free()

@@ -1,5 +1,5 @@
-"""Acceptance words drawn in the first sweeps of a sim and ahead of the later ones: a short call, one that reaches the
-tenth sweep, and a short one again, against the oracle, bit for bit; one workgroup per word (2D and 3D, on
+"""Acceptance words drawn in the first sweeps of a sim and ahead of the later ones: a short ka_run, one that reaches the
+tenth sweep, and a short ka_sweep, against the oracle, bit for bit; one workgroup per word (2D and 3D, on
 register blocks and in LDS) and tiles with one, two and three sweeps a launch, both noise modes."""
 import numpy as np
 import pytest
@@ -20,8 +20,8 @@ def test_calls_on_both_sides_of_the_tenth_sweep(oracle, d, L, W, noise):
     ka.ka_set_option(sim, ka.KA_OPT_NOISE, noise)
     replicas = sorted({0, R - 1})
     orc = oracle.Sim(og, d, K, 9 + L, replicas, shared=bool(noise))
-    for n in (3, 9, 1):
-        ka.ka_sweep(sim, n)
+    for call, n in ((ka.ka_run, 3), (ka.ka_run, 9), (ka.ka_sweep, 1)):
+        call(sim, n if call is ka.ka_sweep else [orc.t + n])
         orc.sweep(n)
         words, _, f, t = ka.ka_get_state(sim)
         assert t == orc.t
